@@ -74,7 +74,9 @@ typedef enum {
 /* GEMM routes.  All compute the same int32 result. */
 enum {
   APT_ROUTE_AUTO = 0,       /* let apt_select_config decide */
-  APT_ROUTE_XOR = 1,        /* XOR + popcount on packed words, cross-lane reduction (Sec. III-B, 1-bit XOR form) */
+  APT_ROUTE_XOR = 1,        /* XOR + popcount on packed words, cross-lane reduction (Sec. III-B, 1-bit XOR form);
+                               with its launch shape left open (mt, waves_m and waves_n all 0) and M >= 2 the
+                               library runs a few-token kernel on the matrix cores instead where that is faster */
   APT_ROUTE_PM1_MFMA = 2,   /* every (i, j) plane pair as +-1 int8 operands on the int8 matrix cores */
   APT_ROUTE_INT8_MFMA = 3,  /* planes reassembled in LDS into one int8 operand, one int8 MFMA per element pair */
   APT_ROUTE_FP4_MFMA = 4,   /* as APT_ROUTE_INT8_MFMA with the bipolar values as operands of the
@@ -182,8 +184,9 @@ apt_status_t apt_quantize_pack_activations_fp16(const uint16_t* a_fp16, int M, i
 
 /* Host-only.  Chooses the route and tile shape for (M, N, K, p, q) (Sec. V-B:
  * lookup table, approximate matching): the config apt_search_config recorded
- * for exactly this problem, if any; otherwise the XOR route for M <= 8, and
- * above that a model of the MI355X kernels (rounds of resident tiles per
+ * for exactly this problem, if any; otherwise the XOR route for M <= 8 (and
+ * for larger M where its kernels, the few-token one among them, are modelled
+ * faster), and above that a model of the MI355X kernels (rounds of resident tiles per
  * compute unit, measured cycles per chunk pair of each tile shape, stream-K
  * partial traffic; the FP4 route only with FP4 activations, q <= 2; the XOR
  * route when its cost per word pair and p*q beats them on small problems),

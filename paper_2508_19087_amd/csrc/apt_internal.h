@@ -120,6 +120,21 @@ hipError_t launch_gemm_xor_act(const GemmArgs& g, const void* a_src, bool fp16_s
                                uint16_t* a_scale_out, const apt_config_t& cfg, hipStream_t stream);
 bool xor_act_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool fp16_src);
 
+// The few-token GEMM on the matrix cores (gemm_thin.hip): its modelled time,
+// infinity where it is not built for a problem (it takes M <= 128 on packed
+// activations, M <= 8 on unpacked ones), and its launches.  The XOR route runs
+// it where the config leaves the launch shape to the library and it is the
+// faster of the two (thin_preferred).
+double thin_us(int M, int N, int K, int p, int q, bool unpacked);
+hipError_t launch_gemm_thin(const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_thin_act(const GemmArgs& g, const void* a_src, bool fp16_src, uint16_t* a_scale_out,
+                                hipStream_t s);
+bool thin_preferred(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool unpacked);
+// Modelled microseconds of the XOR + popcount kernel (select.hip).
+double model_xor_us(int M, int N, int K, int p, int q);
+// Compute units of the current device (select.hip).
+int compute_units();
+
 // Activations given unpacked (int8 codes, or fp16 values quantized per row)
 // to a route that builds its operand bytes itself: the int8-format MFMA route
 // writes its fragments, row sums (and fp16 scales) straight from them

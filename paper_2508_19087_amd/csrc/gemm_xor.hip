@@ -1,6 +1,7 @@
 // gemm_xor.hip - launch geometry and dispatch of the XOR + popcount route;
 // the kernel is in gemm_xor.h.
 #include <algorithm>
+#include <cmath>
 
 #include "gemm_xor.h"
 
@@ -108,6 +109,26 @@ bool xor_act_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg
   return L.lds && L.grid.x <= 0x7fffffffu && L.grid.y <= 65535u;
 }
 
+// The few-token GEMM on the matrix cores takes the call when the config leaves
+// the launch shape open and it is the faster one (cold weights on MI355X).  One
+// token stays on XOR + popcount, which has every weight load in flight at once
+// and no operands to build (W2A4 4096 x 4096 3.4 against 4.8 us, 22016 x 4096
+// 6.4 against 8.2; W4A4 22016 x 4096 10.8 against 11.3).  From two tokens on the
+// popcounts decide: W4A4 22016 x 4096 14.3 against 11.3 us for two tokens and
+// 34.7 against 11.4 for eight; W2A2 1024 x 1024 the other way round, 2.7 against
+// 3.9 us for eight.  Up to 8 tokens the two models are compared (the XOR one is
+// 10% high where they meet), except where one token per wave makes many waves
+// (W1A1 4096 x 1024, 8 tokens: 4.6 against 3.9); above, XOR keeps the small
+// problems (32 tokens at 1024 x 1024, W2A2: 3.8 against 4.9; 64 tokens at
+// 4096 x 1024: 15.6 against 7.4).
+bool thin_preferred(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool unpacked) {
+  if (M < 2 || cfg.mt != 0 || cfg.waves_m != 0 || cfg.waves_n != 0) return false;
+  const double us = thin_us(M, N, K, p, q, unpacked);
+  if (us == HUGE_VAL) return false;
+  if (M > 8) return (int64_t)M * N > 32768 || (double)M * N * K * p * q > 6e8;
+  return (N < 8192 && M * N >= 32768) || us < 0.9 * model_xor_us(M, N, K, p, q);
+}
+
 namespace {
 
 hipError_t launch_xor(const XorParams& prm, const XorLaunch& L, hipStream_t stream);
@@ -115,6 +136,7 @@ hipError_t launch_xor(const XorParams& prm, const XorLaunch& L, hipStream_t stre
 }  // namespace
 
 hipError_t launch_gemm_xor(const GemmArgs& g, const apt_config_t& cfg, hipStream_t stream) {
+  if (thin_preferred(g.M, g.N, g.K, g.p, g.q, cfg, false)) return launch_gemm_thin(g, stream);
   XorParams prm;
   prm.g = g;
   prm.nchunks = num_chunks(g.K);
@@ -129,6 +151,8 @@ hipError_t launch_gemm_xor(const GemmArgs& g, const apt_config_t& cfg, hipStream
 
 hipError_t launch_gemm_xor_act(const GemmArgs& g, const void* a_src, bool fp16_src,
                                uint16_t* a_scale_out, const apt_config_t& cfg, hipStream_t stream) {
+  if (thin_preferred(g.M, g.N, g.K, g.p, g.q, cfg, true))
+    return launch_gemm_thin_act(g, a_src, fp16_src, a_scale_out, stream);
   XorParams prm;
   prm.g = g;
   prm.nchunks = num_chunks(g.K);

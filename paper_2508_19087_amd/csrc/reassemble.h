@@ -25,13 +25,14 @@
 
 namespace apt {
 
-// (a & mask) | (b & ~mask) as one v_bfi_b32.  Written as an instruction so
-// that the compiler keeps one select per merge instead of distributing the
-// masks over the tree, which costs about twice the instructions.
+// (a & mask) | (b & ~mask) as one v_bitop3_b32 (truth table 0xCA: mask ? a : b).
+// Written as the instruction's builtin so that the compiler keeps one select
+// per merge instead of distributing the masks over the tree, which costs
+// about twice the instructions; and not as inline asm, whose result an MFMA
+// may not read in the next two issue slots, a wait the compiler only inserts
+// after instructions that it knows.
 __device__ __forceinline__ uint32_t bsel(uint32_t mask, uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(a), "v"(b));
-  return r;
+  return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xCA);
 }
 
 // The tree in two halves, so that a caller can spread one word's work over
@@ -189,6 +190,68 @@ __device__ __forceinline__ void fp6_word(const uint32_t* pw, uint32_t out[6]) {
   out[3] = y[4] | (y[5] << 24);
   out[4] = (y[5] >> 8) | (y[6] << 16);
   out[5] = (y[6] >> 16) | (y[7] << 8);
+}
+
+// Packed six-bit fields of the 32 elements of six code planes c[0..5] (bit i
+// of an element's field in plane i): 192 bits in out[0..5], the operand order
+// of a 6-bit format.  Pairs of planes merge into 2-bit slots, the even and the
+// odd elements apart (16 slots each), and a 96-bit run of fields takes every
+// third slot of the three pair words: field f's first slot is slot 3 f mod 16
+// of some element, where the low pair already holds that element, the middle
+// pair one slot and the high pair two slots further (rotations), so three
+// selects with constant masks build three dwords.  The element order is the
+// same for every operand and therefore never shows in a dot product.
+__device__ __forceinline__ void six_bit_merge(uint32_t x, uint32_t y, uint32_t z, uint32_t out[3]) {
+  // slots 0, 3, .. / 1, 4, .. / 2, 5, .. of a dword
+  const uint32_t s0 = 0xC30C30C3u, s1 = 0x0C30C30Cu, s2 = 0x30C30C30u;
+  const uint32_t ry = (y << 2) | (y >> 30), rz = (z << 4) | (z >> 28);
+  out[0] = bsel(s0, x, bsel(s1, ry, rz));
+  out[1] = bsel(s2, x, bsel(s0, ry, rz));
+  out[2] = bsel(s1, x, bsel(s2, ry, rz));
+}
+
+__device__ __forceinline__ void six_bit_fields(const uint32_t c[6], uint32_t out[6]) {
+  const uint32_t m1 = 0x55555555u;
+  six_bit_merge(bsel(m1, c[0], c[1] << 1), bsel(m1, c[2], c[3] << 1), bsel(m1, c[4], c[5] << 1), out);
+  six_bit_merge(bsel(m1, c[0] >> 1, c[1]), bsel(m1, c[2] >> 1, c[3]), bsel(m1, c[4] >> 1, c[5]), out + 3);
+}
+
+// The same for the B <= 4 planes of the words u themselves.  E2M3 is linear
+// over its first 16 codes (code c is c / 8: eight subnormals, then 1 + m / 8),
+// so the word u, zero-extended to six bits, is the exact number u / 8 and the
+// rebuild is the merge alone (22 instructions at 4 planes, 10 at 2, where the
+// byte tree takes 28 and 20).
+template <int B>
+__device__ __forceinline__ void six_bit_word(const uint32_t* pw, uint32_t out[6]) {
+  static_assert(B >= 1 && B <= 4, "E2M3 is linear over 16 codes");
+  const uint32_t m1 = 0x55555555u, s0 = 0xC30C30C3u, s1 = 0x0C30C30Cu, s2 = 0x30C30C30u;
+  uint32_t x[2], y[2];
+  if (B == 1) {
+    x[0] = pw[0] & m1;
+    x[1] = (pw[0] >> 1) & m1;
+  } else {
+    x[0] = bsel(m1, pw[0], pw[1] << 1);
+    x[1] = bsel(m1, pw[0] >> 1, pw[1]);
+  }
+  if (B >= 3) {
+    const uint32_t p2 = pw[2], p3 = B == 4 ? pw[3] : 0u;
+    y[0] = B == 4 ? bsel(m1, p2, p3 << 1) : p2 & m1;
+    y[1] = B == 4 ? bsel(m1, p2 >> 1, p3) : (p2 >> 1) & m1;
+  }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    uint32_t* o = out + 3 * h;
+    if (B <= 2) {
+      o[0] = x[h] & s0;
+      o[1] = x[h] & s2;
+      o[2] = x[h] & s1;
+    } else {
+      const uint32_t ry = (y[h] << 2) | (y[h] >> 30);
+      o[0] = (x[h] & s0) | (ry & s1);
+      o[1] = (x[h] & s2) | (ry & s0);
+      o[2] = (x[h] & s1) | (ry & s2);
+    }
+  }
 }
 
 // FP8 operand bytes (OCP E4M3: sign bit 7, exponent bits 6..3 with bias 7,

@@ -175,6 +175,132 @@ __device__ __forceinline__ uint16_t row_scale(uint32_t absmax_bits, float& rh, f
   return __half_as_ushort(s16);
 }
 
+// Largest value and sum over the wave's 64 lanes, uniform: four DPP steps give
+// every 16-lane row its result, four lane reads the wave's.
+template <class Op>
+__device__ __forceinline__ uint32_t wave_fold(uint32_t v, Op op) {
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));   // lane ^ 1
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));   // lane ^ 2
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));  // the row's half mirrored
+  v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));  // the row mirrored
+  const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16);
+  const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+  return op(op(a, b), op(c, d));
+}
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {
+  return wave_fold(v, [](uint32_t x, uint32_t y) { return max(x, y); });
+}
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+  return wave_fold(v, [](uint32_t x, uint32_t y) { return x + y; });
+}
+
+// The same conversions with the bit width in a register (the few-token GEMM
+// is not instantiated per activation width).
+__device__ __forceinline__ void code_words(const uint32_t d[4], int b, uint32_t u[4]) {
+  const uint32_t field = ((1u << b) - 1u) * 0x01010101u;
+  const uint32_t flip = (1u << (b - 1)) * 0x01010101u;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) u[t] = (d[t] & field) ^ flip;
+}
+
+// A row's quantizer: its scale from the largest magnitude's fp16 bits, and the
+// words of 16 of its values.
+//
+// Short form (b <= 7 and a normal scale): with h = x / (2 s), the word is
+// u = floor(h) + 2^(b-1), and no clamp is needed (|h| <= (2^b - 1)/2 (1 + 2^-11)).
+// One fma per value gives f = x / (2 s) + 2^(b-1) + 128 rounded to multiples of
+// 2^-16, whose bits 16..22 are u: the reciprocal's rounding moves h by at most
+// 2^-18, so an integer h rounds back to itself, and h is never close below an
+// integer, since x and s have 11-bit significands: for |h| >= 1/2 a non-integer
+// h is at least 2^-12 away from every integer.  Negative
+// values above -s, where h comes arbitrarily close below 0, are first replaced
+// by -s (same word: h in [-1/2, 0)), as signed 16-bit integers, and -0 by +0.
+// The long form is the exact quotient of HalfRow::words; both give the same
+// words for every finite input (checked over all of them on the CPU).
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+
+// Largest and smallest of a lane's fp16 values (two dwords per packed
+// three-operand instruction), and from them the largest magnitude's bits.
+struct HalfExtremes {
+  half2_t hi = {(_Float16)0.0f, (_Float16)0.0f}, lo = {(_Float16)0.0f, (_Float16)0.0f};
+  __device__ __forceinline__ void fold(const uint32_t d[8]) {
+#pragma unroll
+    for (int t = 0; t < 8; t += 2) {
+      const half2_t x = __builtin_bit_cast(half2_t, d[t]), y = __builtin_bit_cast(half2_t, d[t + 1]);
+      hi = __builtin_elementwise_maximum(__builtin_elementwise_maximum(hi, x), y);
+      lo = __builtin_elementwise_minimum(__builtin_elementwise_minimum(lo, x), y);
+    }
+  }
+  __device__ __forceinline__ uint32_t largest_magnitude() const {
+    const uint32_t h = __builtin_bit_cast(uint32_t, hi) & 0x7FFF7FFFu, l = __builtin_bit_cast(uint32_t, lo) & 0x7FFF7FFFu;
+    return max(max(h & 0xFFFFu, h >> 16), max(l & 0xFFFFu, l >> 16));
+  }
+};
+
+struct Quantizer {
+  uint16_t scale;
+  int b;
+  bool quick;
+  float rh, s2, base;
+  uint32_t least;  // -s in both halves of a dword
+
+  __device__ __forceinline__ void set(uint32_t absmax_bits, int bits) {
+    b = bits;
+    const float absmax = __half2float(__ushort_as_half((unsigned short)absmax_bits));
+    const __half s16 = __float2half_rn(__fdiv_rn(absmax, (float)((1 << b) - 1)));
+    const float s = __half2float(s16);
+    scale = __half_as_ushort(s16);
+    rh = s > 0.0f ? __fdiv_rn(1.0f, s) * 0.5f : 0.0f;
+    s2 = s * 2.0f;
+    quick = b <= 7 && scale >= 0x0400u;  // (uniform where the row is)
+    base = 128.0f + (float)(1 << (b - 1));
+    least = (0x8000u | scale) * 0x00010001u;
+  }
+
+  // Short form: f[j], whose bits 16..22 are the word of value j.
+  __device__ __forceinline__ void quick_bits(const uint32_t d[8], uint32_t f[16]) const {
+    typedef short short2_t __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int t = 0; t < 8; ++t) {
+      const half2_t x0 = __builtin_bit_cast(half2_t, d[t]) + half2_t{(_Float16)0.0f, (_Float16)0.0f};
+      const half2_t x = __builtin_bit_cast(
+          half2_t, __builtin_elementwise_max(__builtin_bit_cast(short2_t, x0), __builtin_bit_cast(short2_t, least)));
+      f[2 * t] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.x, rh, base));
+      f[2 * t + 1] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.y, rh, base));
+    }
+  }
+  // The words (bits 16..22) of four values in one dword.
+  __device__ static __forceinline__ uint32_t gather(const uint32_t f[4]) {
+    return __builtin_amdgcn_perm(f[1], f[0], 0x0C0C0602u) | __builtin_amdgcn_perm(f[3], f[2], 0x06020C0Cu);
+  }
+
+  __device__ __forceinline__ void exact_words(const uint32_t d[8], uint32_t u[4]) const {
+#pragma clang fp contract(off)
+    const int clo = -(1 << (b - 1)), chi = (1 << (b - 1)) - 1;
+    const uint32_t field = ((1u << b) - 1u) * 0x01010101u;
+    const uint32_t flip = (1u << (b - 1)) * 0x01010101u;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      uint32_t acc = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = 4 * t + q;
+        const uint32_t bits = (d[j / 2] >> (16 * (j % 2))) & 0xFFFFu;
+        const float x = __half2float(__ushort_as_half((unsigned short)bits));
+        const float h0 = __builtin_fmaf(x, rh, 0.0f);
+        const float e = __builtin_fmaf(-h0, s2, x);
+        const float h = __builtin_fmaf(e, rh, h0);  // RN(x / s) / 2
+        int c;
+        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(c) : "v"(h));
+        c = min(max(c, clo), chi);
+        const uint32_t sel = q == 1 ? 0x03020400u : q == 2 ? 0x03040100u : 0x04020100u;
+        acc = q == 0 ? (uint32_t)c : __builtin_amdgcn_perm((uint32_t)c, acc, sel);
+      }
+      u[t] = (acc & field) ^ flip;
+    }
+  }
+};
+
 // This lane's word of plane pair (i, i + 1) after transpose8x8 of its two
 // 8-element groups (lo/hi of elements 0..7 in sa, of 8..15 in sb): the even
 // lane of a pair gets the 32 bits of plane i, the odd lane those of plane i + 1

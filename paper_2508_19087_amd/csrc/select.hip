@@ -67,6 +67,8 @@ constexpr int kFirstTail = 2;
 // (bytes per microsecond), as the stream-K launches measured on MI355X show.
 constexpr double kPartialBytesPerUs = 2.5e6;
 
+}  // namespace
+
 int compute_units() {
   static int cus = 0;
   if (cus == 0) {
@@ -79,6 +81,8 @@ int compute_units() {
   }
   return cus;
 }
+
+namespace {
 
 apt_config_t base_config(int route) {
   apt_config_t c;
@@ -146,20 +150,26 @@ double model_us(const Int8Shape& s, int f, int M, int N, int K, int grid, int cu
   return model_loop_us(s, f, M, N, K, grid, cus) + s.t[f].fixed_us;
 }
 
-// The tail shape a split config with main shape i and tail size of shape t
-// runs: of the shapes of that size, the one with the main shape's wave count
-// (the library's rule), else t itself.
-// Modelled microseconds of the XOR route (8 activation rows per block row):
-// a fixed part and a cost per 32-bit word pair of an 8-row activation block
-// and one weight row, rising with the activation planes read from LDS (q) and
-// with the p*q plane products.  Fitted (least squares on the relative error)
-// to MI355X timings for M = 16 to 256, N and K from 1024 to 14336 and p*q
-// from 2 to 16: median error 8%.
+}  // namespace
+
+// Modelled microseconds of the XOR route: a fixed part, and for up to 8 tokens
+// the weight stream and the popcounts (least squares on the relative error over
+// cold timings of M = 2..8, N, K = 512..11008, p*q = 1..16: median error 6%);
+// above that a cost per 32-bit word pair of an 8-row activation block and one
+// weight row, rising with the activation planes read from LDS (q) and with the
+// p*q plane products (M = 16 to 256, N and K from 1024 to 14336, p*q from 2 to
+// 16: median error 8%).
 double model_xor_us(int M, int N, int K, int p, int q) {
+  if (M <= 8) return 2.55 + (double)N * K * (0.0256e-6 * p + (double)M * q * (1.42 * p + 4.23) * 1e-9);
   const double words = 8.0 * ((M + 7) / 8) * (double)N * K / 32.0;
   return 3.564 + words * (-0.2140 + 0.1792 * q + 0.0439 * p * q) * 1e-6;
 }
 
+namespace {
+
+// The tail shape a split config with main shape i and tail size of shape t
+// runs: of the shapes of that size, the one with the main shape's wave count
+// (the library's rule), else t itself.
 bool tail_runs_as(int i, int t) {
   const Int8Shape &m = kInt8Shapes[i], &ts = kInt8Shapes[t];
   for (int u = 0; u < kNumInt8Shapes; ++u) {
@@ -405,11 +415,15 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
       }
     }
   }
-  // small problems: the XOR route's single launch against the MFMA routes'
-  // fixed costs.  The MFMA figures were measured with every compute unit
+  // few tokens or small problems: the XOR route's single launch (XOR +
+  // popcount, or the few-token GEMM it runs) against the MFMA routes' fixed
+  // costs.  The MFMA figures were measured with every compute unit
   // busy and overstate grids of a few tiles by 10-40%, so they count at 90%
   // here (measured over M = 16..256, N, K = 1024..14336, p*q = 2..16).
-  if (model_xor_us(M, N, K, p, q) < 0.9 * best) return base_config(APT_ROUTE_XOR);
+  const apt_config_t open = base_config(APT_ROUTE_XOR);
+  const double few = thin_preferred(M, N, K, p, q, open, false) ? thin_us(M, N, K, p, q, false)
+                                                                : model_xor_us(M, N, K, p, q);
+  if (few < 0.9 * best) return open;
   const Int8Shape& s = kInt8Shapes[best_i];
   apt_config_t c = base_config(best_fp4 ? APT_ROUTE_FP4_MFMA : APT_ROUTE_INT8_MFMA);
   c.bm = s.bm;
