@@ -96,7 +96,11 @@ enum {
  *   route      APT_ROUTE_*
  *   bm, bn     output tile per workgroup (int8 MFMA route: 256x256 with 4x2 or
  *              2x4 waves, 512x128 with 8x1, 256x128 with 4x2 or 4x1, 128x128
- *              with 2x2; the 4-wave shapes run two workgroups per compute unit)
+ *              with 2x2; the 4-wave shapes run two workgroups per compute unit).
+ *              For p, q <= 4 and K (2^p-1)(2^q-1) < 2^24 the 256x128 shape with
+ *              4x1 waves and no split runs another kernel on 128x256 tiles, one
+ *              workgroup per tile whatever grid says (six-bit operands on the
+ *              block-scaled MFMA; the same int32 result)
  *   bk         K elements staged per pipeline step (MFMA routes: 0 or 128)
  *   waves_m, waves_n   wave grid inside a workgroup (int8 MFMA route); XOR
  *              route: waves_m = waves per workgroup, each owning one 8-row

@@ -30,6 +30,7 @@
 #include <type_traits>
 
 #include "apt_internal.h"
+#include "reassemble.h"
 #include "rowcode.h"
 
 namespace apt {
@@ -47,10 +48,14 @@ constexpr int kBlockRows = 32;
 constexpr int kHeldIters = 4;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
+typedef int v2i __attribute__((ext_vector_type(2)));
+// bytes of a six-bit fragment (32 rows of one word: 16 bytes per row, then 8;
+// gemm_int8.h's kSixBytes)
+constexpr int kSixBytes = 768;
 
 template <bool kHalf, bool kVec, int B>
 __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
-    const uint8_t* __restrict__ src, int M, int K, int nchunks, int nsteps, int mblocks,
+    const uint8_t* __restrict__ src, int M, int K, int six, int nchunks, int nsteps, int mblocks,
     v4i* __restrict__ frag, int32_t* __restrict__ rowsum, uint16_t* __restrict__ scale,
     uint16_t* __restrict__ scale_out, int* __restrict__ counters, int ncounters) {
   using Src = typename std::conditional<kHalf, HalfRow<kVec, B>, CodeRow<kVec, B>>::type;
@@ -144,8 +149,17 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
       usum = __builtin_amdgcn_sad_u8(c[t], 0u, usum);
       if (B == 8) c[t] ^= 0x80808080u;
     }
-    // o[t], byte j = element 8 j + t = byte t mod 4 of c[2 j + t / 4]
     uint32_t o[8];
+    if constexpr (B <= 4) {
+      if (six) {
+        six_bit_bytes(c, o);
+        uint8_t* f = reinterpret_cast<uint8_t*>(frag) + ((int64_t)mb * nsteps + w) * kSixBytes;
+        *reinterpret_cast<v4i*>(f + l * 16) = v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+        *reinterpret_cast<v2i*>(f + 512 + l * 8) = v2i{(int)o[4], (int)o[5]};
+        return;
+      }
+    }
+    // o[t], byte j = element 8 j + t = byte t mod 4 of c[2 j + t / 4]
 #pragma unroll
     for (int h = 0; h < 2; ++h) {          // h = t / 4: the odd or even c
 #pragma unroll
@@ -174,6 +188,12 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
   }
   // the chunk that makes the count even: all-zero bytes
   for (int w = words + wave * kWordLanes + wl; w < nsteps; w += step) {
+    if (six) {
+      uint8_t* f = reinterpret_cast<uint8_t*>(frag) + ((int64_t)mb * nsteps + w) * kSixBytes;
+      *reinterpret_cast<v4i*>(f + l * 16) = v4i{0, 0, 0, 0};
+      *reinterpret_cast<v2i*>(f + 512 + l * 8) = v2i{0, 0};
+      continue;
+    }
     v4i* f = frag + ((int64_t)mb * nsteps + w) * kWave;
     f[l] = v4i{0, 0, 0, 0};
     f[l + 32] = v4i{0, 0, 0, 0};
@@ -192,7 +212,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
 }
 
 template <bool kHalf, bool kVec, int B>
-hipError_t launch_one(const void* src, int M, int K, int nchunks, int nsteps, void* frag,
+hipError_t launch_one(const void* src, int M, int K, bool six, int nchunks, int nsteps, void* frag,
                       int32_t* rowsum, uint16_t* scale, uint16_t* scale_out, int* counters,
                       int ncounters, hipStream_t s) {
   const int mblocks = (M + kBlockRows - 1) / kBlockRows;
@@ -204,42 +224,42 @@ hipError_t launch_one(const void* src, int M, int K, int nchunks, int nsteps, vo
   const int cap = kHalf ? kMaxWaves : 8;
   const int waves = std::min(cap, (words + kWordLanes - 1) / kWordLanes);
   return launch_kernel(act_frag_kernel<kHalf, kVec, B>, grid, dim3(waves * kWave), 0, s,
-                       static_cast<const uint8_t*>(src), M, K, nchunks, nsteps, mblocks,
+                       static_cast<const uint8_t*>(src), M, K, (int)six, nchunks, nsteps, mblocks,
                        static_cast<v4i*>(frag), rowsum, scale, scale_out, counters, ncounters);
 }
 
 template <int B>
-hipError_t launch_b(const void* src, bool fp16, bool vec, int M, int K, int nchunks, int nsteps,
+hipError_t launch_b(const void* src, bool fp16, bool vec, int M, int K, bool six, int nchunks, int nsteps,
                     void* frag, int32_t* rowsum, uint16_t* scale, uint16_t* scale_out,
                     int* counters, int ncounters, hipStream_t s) {
   if (fp16)
-    return vec ? launch_one<true, true, B>(src, M, K, nchunks, nsteps, frag, rowsum, scale,
+    return vec ? launch_one<true, true, B>(src, M, K, six, nchunks, nsteps, frag, rowsum, scale,
                                            scale_out, counters, ncounters, s)
-               : launch_one<true, false, B>(src, M, K, nchunks, nsteps, frag, rowsum, scale,
+               : launch_one<true, false, B>(src, M, K, six, nchunks, nsteps, frag, rowsum, scale,
                                             scale_out, counters, ncounters, s);
-  return vec ? launch_one<false, true, B>(src, M, K, nchunks, nsteps, frag, rowsum, scale,
+  return vec ? launch_one<false, true, B>(src, M, K, six, nchunks, nsteps, frag, rowsum, scale,
                                           scale_out, counters, ncounters, s)
-             : launch_one<false, false, B>(src, M, K, nchunks, nsteps, frag, rowsum, scale,
+             : launch_one<false, false, B>(src, M, K, six, nchunks, nsteps, frag, rowsum, scale,
                                            scale_out, counters, ncounters, s);
 }
 
 }  // namespace
 
-hipError_t launch_act_frag(const void* src, bool fp16, int M, int K, int q, int nsteps, void* frag,
+hipError_t launch_act_frag(const void* src, bool fp16, int M, int K, int q, bool six, int nsteps, void* frag,
                            int32_t* rowsum, uint16_t* scale, uint16_t* scale_out, int* counters,
                            int ncounters, hipStream_t s) {
   const int nchunks = num_chunks(K);
   // 16-byte loads: every row starts 16-byte aligned and holds whole vectors
   const bool vec = (reinterpret_cast<uintptr_t>(src) & 15u) == 0 && K % 16 == 0;
   switch (q) {
-    case 1: return launch_b<1>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 2: return launch_b<2>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 3: return launch_b<3>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 4: return launch_b<4>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 5: return launch_b<5>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 6: return launch_b<6>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 7: return launch_b<7>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
-    case 8: return launch_b<8>(src, fp16, vec, M, K, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 1: return launch_b<1>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 2: return launch_b<2>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 3: return launch_b<3>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 4: return launch_b<4>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 5: return launch_b<5>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 6: return launch_b<6>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 7: return launch_b<7>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
+    case 8: return launch_b<8>(src, fp16, vec, M, K, six, nchunks, nsteps, frag, rowsum, scale, scale_out, counters, ncounters, s);
   }
   return hipErrorInvalidValue;
 }

@@ -61,6 +61,11 @@ inline bool fp8_route_ok(int K, int p, int q) {
   return p <= 4 && q <= 4 &&
          (int64_t)num_chunks(K) * kChunk * ((1 << p) - 1) * ((1 << q) - 1) < ((int64_t)1 << 24);
 }
+// Six-bit E2M3 codes hold words of at most 4 bits (as u / 8), and the fp32 sums
+// of their products stay exact integers (padding words are 0).
+inline bool six_bit_ok(int K, int p, int q) {
+  return p <= 4 && q <= 4 && (int64_t)K * ((1 << p) - 1) * ((1 << q) - 1) < ((int64_t)1 << 24);
+}
 // Routes that run the reassembled MFMA kernels (operand formats int8, FP4, FP6, FP8).
 inline bool mfma_route(int route) {
   return route == APT_ROUTE_INT8_MFMA || route == APT_ROUTE_FP4_MFMA || route == APT_ROUTE_FP6_MFMA ||
@@ -146,18 +151,19 @@ struct ActSource {
   uint16_t* scale;     // device [M]: receives the fp16 source's scales
   uint16_t* scale_out; // device [M] or NULL: a copy of them for the caller
 };
-hipError_t launch_act_frag(const void* src, bool fp16, int M, int K, int q, int nsteps, void* frag,
+hipError_t launch_act_frag(const void* src, bool fp16, int M, int K, int q, bool six, int nsteps, void* frag,
                            int32_t* rowsum, uint16_t* scale, uint16_t* scale_out, int* counters,
                            int ncounters, hipStream_t s);
 
 // Reassembled int8 MFMA route (gemm_int8.hip).  The workspace holds the
 // activations expanded into MFMA fragments (int8_workspace_bytes): from the
-// packed planes (src NULL), or, with the int8 operand format only, from an
-// unpacked source (g.a_rowsum and g.a_scale must then name src's outputs).
+// packed planes (src NULL), or, on the int8 route, from an unpacked source (g.a_rowsum and g.a_scale must then name src's outputs).
 hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* workspace,
                             hipStream_t stream, const ActSource* src = nullptr);
 // Operand format of the activations in a config of the MFMA routes (0: int8).
 int int8_operand_format(const apt_config_t& cfg, int q);
+// Whether an int8-route config runs gemm_direct.h's kernel on six-bit codes.
+bool int8_runs_direct(const apt_config_t& cfg, int K, int p, int q);
 constexpr int kMaxGrid = 4096;  // persistent workgroups of the int8 route, at most
 bool int8_config_ok(const apt_config_t& cfg, int N);
 bool int8_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg);

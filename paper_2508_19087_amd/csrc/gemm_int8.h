@@ -88,6 +88,10 @@ struct Fmt {
   static constexpr int kAVecs = F >= 2 ? 2 : 1;                // 16-byte activation vectors per lane and k-step
 };
 constexpr int kStages = 3;                      // weight LDS ring depth
+// F = 5: the words u of at most 4 bits as six-bit E2M3 codes (u / 8) on both
+// sides (gemm_direct.h); a fragment is 32 rows of one word, 16 bytes per row and then 8 bytes per row.
+constexpr int kSixFormat = 5;
+constexpr int kSixBytes = 768;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
@@ -141,6 +145,7 @@ struct Int8Params {
 // fmt (F = 1: nibbles, otherwise bytes).
 inline size_t a_frag_bytes(int M, int K, int fmt = 0) {
   const int nce = (num_chunks(K) + 1) & ~1;
+  if (fmt == kSixFormat) return (size_t)((M + 31) / 32) * nce * kWordsPerPlane * kSixBytes;
   return (size_t)((M + 31) / 32) * 32 * nce * (fmt == 1 ? kChunk / 2 : kChunk);
 }
 
@@ -185,7 +190,7 @@ __global__ __launch_bounds__(256) void expand_a_kernel(const uint32_t* __restric
   const int w = t % kWordsPerPlane;
   const int row = t / kWordsPerPlane;
   const int chunk = blockIdx.y;
-  constexpr int kSteps = Fmt<F>::kSteps;
+  constexpr int kSteps = F == kSixFormat ? kWordsPerPlane : Fmt<F == kSixFormat ? 0 : F>::kSteps;
   uint32_t pw[Q];
   if (row < M && chunk < nchunks) {
     const uint32_t* src = a_packed + plane_words(row, chunk, 0, nchunks, Q) + w;
@@ -196,7 +201,13 @@ __global__ __launch_bounds__(256) void expand_a_kernel(const uint32_t* __restric
     for (int j = 0; j < Q; ++j) pw[j] = 0u;
   }
   const int mb = row / 32, l = row % 32;
-  if (F == 4) {
+  if (F == kSixFormat) {
+    uint32_t o[6];
+    six_bit_word<(Q <= 4 ? Q : 4)>(pw, o);  // (all-zero planes: all-zero codes)
+    uint8_t* f = reinterpret_cast<uint8_t*>(out) + ((int64_t)mb * nsteps + chunk * kSteps + w) * kSixBytes;
+    *reinterpret_cast<v4i*>(f + l * 16) = v4i{(int)o[0], (int)o[1], (int)o[2], (int)o[3]};
+    *reinterpret_cast<v2i*>(f + 512 + l * 8) = v2i{(int)o[4], (int)o[5]};
+  } else if (F == 4) {
     // word w -> k-step w / 2, lane half w mod 2; vector 0 holds operand dwords
     // 0..3, vector 1 dwords 4..7
     uint32_t o[8] = {0u, 0u, 0u, 0u, 0u, 0u, 0u, 0u};
@@ -1026,6 +1037,9 @@ constexpr TileShape kShapes[] = {
     {256, 128, 4, 1, 2},
 };
 constexpr int kNumShapes = sizeof(kShapes) / sizeof(kShapes[0]);
+// The shape that gemm_direct.h's kernel takes over for operands of at most 4
+// bits: the same workgroup size and area.
+constexpr int kDirectShape = 5;
 
 // LDS of shape S: the weight ring, the epilogue terms and one 32x32 int32
 // epilogue slot per wave.

@@ -2,6 +2,7 @@
 // reassembled-int8 MFMA route; the kernels are in gemm_int8.h.
 #include <algorithm>
 
+#include "gemm_direct.h"
 #include "gemm_int8.h"
 
 namespace apt {
@@ -30,6 +31,16 @@ hipError_t launch_p(int p, int fmt, int shape, const Int8Params& prm, int grid,
     case 6: return launch_for_p<6>(fmt, shape, prm, grid, stream);
     case 7: return launch_for_p<7>(fmt, shape, prm, grid, stream);
     case 8: return launch_for_p<8>(fmt, shape, prm, grid, stream);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_direct(int p, const Int8Params& prm, hipStream_t stream) {
+  switch (p) {
+    case 1: return direct::launch_for_p<1>(prm, stream);
+    case 2: return direct::launch_for_p<2>(prm, stream);
+    case 3: return direct::launch_for_p<3>(prm, stream);
+    case 4: return direct::launch_for_p<4>(prm, stream);
   }
   return hipErrorInvalidValue;
 }
@@ -176,13 +187,22 @@ size_t int8_workspace_bytes(int M, int N, int K, int q, const apt_config_t& cfg)
 
 int int8_operand_format(const apt_config_t& cfg, int q) { return int8::operand_format(cfg, q); }
 
+// The 256 x 128 (4 x 1) shape of the int8 route, in one launch, where the
+// operands fit six-bit codes and the fp32 sums stay exact: gemm_direct.h.  Its
+// fragments take three quarters of the workspace that the int8 ones do.
+bool int8_runs_direct(const apt_config_t& cfg, int K, int p, int q) {
+  return cfg.route == APT_ROUTE_INT8_MFMA && cfg.split_n == 0 && int8::shape_index(cfg) == int8::kDirectShape &&
+         six_bit_ok(K, p, q);
+}
+
 hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* workspace,
                             hipStream_t stream, const ActSource* src) {
   using namespace int8;
   Plan pl[2];
   const int nl = make_plans(g.M, g.N, g.K, cfg, pl);
   Int8Params prm[2];
-  const int fmt = operand_format(cfg, g.q);
+  const bool six = int8_runs_direct(cfg, g.K, g.p, g.q);
+  const int fmt = six ? kSixFormat : operand_format(cfg, g.q);
   uint8_t* base = static_cast<uint8_t*>(workspace) + align256(a_frag_bytes(g.M, g.K, fmt));
   int* counters = nullptr;
   int ncounters = 0;
@@ -190,14 +210,14 @@ hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* wo
     Int8Params& p = prm[i];
     p.g = g;
     p.nchunks = num_chunks(g.K);
-    p.nsteps = ((p.nchunks + 1) & ~1) * (fmt ? Fmt<1>::kSteps : Fmt<0>::kSteps);
+    p.nsteps = ((p.nchunks + 1) & ~1) * (fmt == 0 || six ? Fmt<0>::kSteps : Fmt<1>::kSteps);
     p.mblocks = (g.M + 31) / 32;
     p.a_frag = static_cast<const v4i*>(workspace);
     p.a_bytes = (uint32_t)a_frag_bytes(g.M, g.K, fmt);
     p.w_bytes = (uint32_t)apt_packed_bytes(g.N, g.K, g.p);
     p.n_begin = pl[i].n_begin;
-    p.tiles_n = pl[i].tiles_n;
-    p.tiles = pl[i].tiles;
+    p.tiles_n = six ? (g.N + direct::kBN - 1) / direct::kBN : pl[i].tiles_n;
+    p.tiles = six ? (g.M + direct::kBM - 1) / direct::kBM * p.tiles_n : pl[i].tiles;
     p.dp_tiles = pl[i].dp_tiles;
     p.sk_pairs = pl[i].sk_pairs;
     p.sk_grid = pl[i].sk_grid;
@@ -220,8 +240,8 @@ hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* wo
   const Int8Params& p0 = prm[0];
   hipError_t e = hipErrorInvalidValue;
   if (src != nullptr) {
-    if (fmt != 0) return hipErrorInvalidValue;
-    e = launch_act_frag(src->data, src->fp16, g.M, g.K, g.q, p0.nsteps, frag, src->rowsum,
+    if (fmt != 0 && !six) return hipErrorInvalidValue;
+    e = launch_act_frag(src->data, src->fp16, g.M, g.K, g.q, six, p0.nsteps, frag, src->rowsum,
                         src->scale, src->scale_out, counters, ncounters, stream);
   } else switch (g.q) {
     case 1: e = launch_expand_for_q<1>(fmt, g.a_packed, g.M, p0.nchunks, p0.nsteps, p0.mblocks, frag, counters, ncounters, stream); break;
@@ -234,6 +254,7 @@ hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* wo
     case 8: e = launch_expand_for_q<8>(fmt, g.a_packed, g.M, p0.nchunks, p0.nsteps, p0.mblocks, frag, counters, ncounters, stream); break;
   }
   if (e != hipSuccess) return e;
+  if (six) return launch_direct(g.p, prm[0], stream);
   if (nl == 2 && pair_supported(pl[0].shape, pl[1].shape))
     return launch_pair(g.p, fmt, pl[0].shape, prm[0], pl[0].grid, pl[1].shape, prm[1], pl[1].grid,
                        stream);

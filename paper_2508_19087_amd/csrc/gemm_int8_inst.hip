@@ -46,7 +46,8 @@ hipError_t launch_expand(const uint32_t* a_packed, int M, int nchunks, int nstep
                          v4i* out, int* counters, int ncounters, hipStream_t stream) {
   // x: (row, word) pairs of one chunk; y: the chunks (an even count)
   const int blocks = (mblocks * 32 * kWordsPerPlane + 255) / 256;
-  return launch_kernel(expand_a_kernel<Q, F>, dim3(blocks, nsteps / Fmt<F>::kSteps), dim3(256), 0,
+  constexpr int steps = F == kSixFormat ? kWordsPerPlane : Fmt<F == kSixFormat ? 0 : F>::kSteps;
+  return launch_kernel(expand_a_kernel<Q, F>, dim3(blocks, nsteps / steps), dim3(256), 0,
                        stream, a_packed, M, nchunks, nsteps, mblocks, out, counters, ncounters);
 }
 
@@ -73,6 +74,9 @@ hipError_t launch_expand_for_q(int fmt, const uint32_t* a_packed, int M, int nch
                                  stream);
   }
   if constexpr (Q <= 4) {
+    if (fmt == kSixFormat)
+      return launch_expand<Q, kSixFormat>(a_packed, M, nchunks, nsteps, mblocks, out, counters, ncounters,
+                                          stream);
     if (fmt == 4)
       return launch_expand<Q, 4>(a_packed, M, nchunks, nsteps, mblocks, out, counters, ncounters,
                                  stream);

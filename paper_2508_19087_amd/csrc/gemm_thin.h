@@ -261,16 +261,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_thin_kernel(ThinParams 
     // the operand's bytes from the words' bytes in element order
     auto order = [&](const uint32_t (&c)[8], uint32_t (&o)[8]) __attribute__((always_inline)) {
       if constexpr (C == kLow) {
-        auto pair = [&](int x, int y) {  // [x.b0, y.b2, x.b1, y.b3]
-          return __builtin_amdgcn_perm(c[y], c[x], 0x07010600u);
-        };
-        const uint32_t p0[8] = {pair(0, 1), pair(3, 4), pair(6, 7), pair(1, 2),
-                                pair(4, 5), pair(7, 0), pair(2, 3), pair(5, 6)};
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          o[t] = __builtin_amdgcn_perm(p0[2 * t + 1], p0[2 * t], 0x05040100u);
-          o[4 + t] = __builtin_amdgcn_perm(p0[2 * t + 1], p0[2 * t], 0x07060302u);
-        }
+        six_bit_order(c, o);
       } else {
         // o[t], byte j = element 8 j + t = byte t mod 4 of c[2 j + t / 4]
 #pragma unroll

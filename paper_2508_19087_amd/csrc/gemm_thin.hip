@@ -23,9 +23,7 @@ bool plan(int M, int N, int K, int p, int q, int src, ThinLaunch* L) {
   const int nc = num_chunks(K);
   // 32-bit offsets below kNowhere
   if (apt_packed_bytes(N, K, p) >= thin::kNowhere || apt_packed_bytes(M, K, q) >= thin::kNowhere) return false;
-  const bool low = p <= 4 && q <= 4 &&
-                   (int64_t)nc * kChunk * ((1 << p) - 1) * ((1 << q) - 1) < ((int64_t)1 << 24);
-  L->cls = low ? thin::kLow : q == 8 ? thin::kByte8 : thin::kByte;
+  L->cls = six_bit_ok(K, p, q) ? thin::kLow : q == 8 ? thin::kByte8 : thin::kByte;
   const int kgroups = (nc + thin::kGroupChunks - 1) / thin::kGroupChunks;
   L->gk = (kgroups + thin::kWaves - 1) / thin::kWaves;
   // the most tokens per workgroup that its registers hold, no more than needed

@@ -221,36 +221,68 @@ __device__ __forceinline__ void six_bit_fields(const uint32_t c[6], uint32_t out
 // so the word u, zero-extended to six bits, is the exact number u / 8 and the
 // rebuild is the merge alone (22 instructions at 4 planes, 10 at 2, where the
 // byte tree takes 28 and 20).
+// In two halves (the even elements' three dwords, the odd elements'), which
+// share nothing.
 template <int B>
-__device__ __forceinline__ void six_bit_word(const uint32_t* pw, uint32_t out[6]) {
+__device__ __forceinline__ void six_bit_half(const uint32_t* pw, int odd, uint32_t out[3]) {
   static_assert(B >= 1 && B <= 4, "E2M3 is linear over 16 codes");
   const uint32_t m1 = 0x55555555u, s0 = 0xC30C30C3u, s1 = 0x0C30C30Cu, s2 = 0x30C30C30u;
-  uint32_t x[2], y[2];
-  if (B == 1) {
-    x[0] = pw[0] & m1;
-    x[1] = (pw[0] >> 1) & m1;
+  auto slots = [&](uint32_t lo, uint32_t hi, bool two) {  // 2-bit slots of a pair of planes
+    if (!two) return (odd ? lo >> 1 : lo) & m1;
+    return odd ? bsel(m1, lo >> 1, hi) : bsel(m1, lo, hi << 1);
+  };
+  const uint32_t x = slots(pw[0], B >= 2 ? pw[B >= 2 ? 1 : 0] : 0u, B >= 2);
+  if (B <= 2) {
+    out[0] = x & s0;
+    out[1] = x & s2;
+    out[2] = x & s1;
   } else {
-    x[0] = bsel(m1, pw[0], pw[1] << 1);
-    x[1] = bsel(m1, pw[0] >> 1, pw[1]);
+    const uint32_t y = slots(pw[B >= 3 ? 2 : 0], B == 4 ? pw[B == 4 ? 3 : 0] : 0u, B == 4);
+    const uint32_t ry = (y << 2) | (y >> 30);
+    out[0] = (x & s0) | (ry & s1);
+    out[1] = (x & s2) | (ry & s0);
+    out[2] = (x & s1) | (ry & s2);
   }
-  if (B >= 3) {
-    const uint32_t p2 = pw[2], p3 = B == 4 ? pw[3] : 0u;
-    y[0] = B == 4 ? bsel(m1, p2, p3 << 1) : p2 & m1;
-    y[1] = B == 4 ? bsel(m1, p2 >> 1, p3) : (p2 >> 1) & m1;
+}
+
+template <int B>
+__device__ __forceinline__ void six_bit_word(const uint32_t* pw, uint32_t out[6]) {
+  six_bit_half<B>(pw, 0, out);
+  six_bit_half<B>(pw, 1, out + 3);
+}
+
+// The same fields from the words' bytes in element order (byte b of c[i]: u < 64
+// of element 4 i + b): the bytes in field order, then four 6-bit codes of a
+// dword to 24 bits and 24 to 32.
+__device__ __forceinline__ void six_bit_order(const uint32_t c[8], uint32_t o[8]) {
+  // fields 0..15 are the even elements 0 6 12 18 | 24 30 4 10 | 16 22 28 2 | 8 14 20 26,
+  // fields 16..31 the odd ones after them
+  auto pair = [&](int x, int y) {  // [x.b0, y.b2, x.b1, y.b3]
+    return __builtin_amdgcn_perm(c[y], c[x], 0x07010600u);
+  };
+  const uint32_t p[8] = {pair(0, 1), pair(3, 4), pair(6, 7), pair(1, 2),
+                         pair(4, 5), pair(7, 0), pair(2, 3), pair(5, 6)};
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    o[t] = __builtin_amdgcn_perm(p[2 * t + 1], p[2 * t], 0x05040100u);
+    o[4 + t] = __builtin_amdgcn_perm(p[2 * t + 1], p[2 * t], 0x07060302u);
+  }
+}
+
+__device__ __forceinline__ void six_bit_bytes(const uint32_t c[8], uint32_t out[6]) {
+  uint32_t o[8], y[8];
+  six_bit_order(c, o);
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint32_t c01 = bsel(0x3Fu, o[t], o[t] >> 2);     // bits 0..11: codes 0, 1
+    const uint32_t c012 = bsel(0xFFFu, c01, o[t] >> 4);    // bits 0..17: codes 0..2
+    y[t] = bsel(0x3FFFFu, c012, o[t] >> 6);                // bits 0..23: codes 0..3
   }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    uint32_t* o = out + 3 * h;
-    if (B <= 2) {
-      o[0] = x[h] & s0;
-      o[1] = x[h] & s2;
-      o[2] = x[h] & s1;
-    } else {
-      const uint32_t ry = (y[h] << 2) | (y[h] >> 30);
-      o[0] = (x[h] & s0) | (ry & s1);
-      o[1] = (x[h] & s2) | (ry & s0);
-      o[2] = (x[h] & s1) | (ry & s2);
-    }
+    out[3 * h] = y[4 * h] | (y[4 * h + 1] << 24);
+    out[3 * h + 1] = (y[4 * h + 1] >> 8) | (y[4 * h + 2] << 16);
+    out[3 * h + 2] = (y[4 * h + 2] >> 16) | (y[4 * h + 3] << 8);
   }
 }
 

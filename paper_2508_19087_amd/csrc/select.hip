@@ -63,6 +63,8 @@ constexpr int kNumInt8Shapes = (int)(sizeof(kInt8Shapes) / sizeof(kInt8Shapes[0]
 // last three); a main and a tail with the same wave count share one launch.
 constexpr int kNumMainShapes = 3;
 constexpr int kFirstTail = 2;
+// The shape that runs on six-bit codes where they hold the operands (gemm_direct.h).
+constexpr int kSixShape = 2;
 // Device-wide rate at which stream-K partial tiles are written and read back
 // (bytes per microsecond), as the stream-K launches measured on MI355X show.
 constexpr double kPartialBytesPerUs = 2.5e6;
@@ -146,6 +148,19 @@ double model_loop_us(const Int8Shape& s, int f, int M, int N, int K, int grid, i
   return us;
 }
 
+// Modelled microseconds of gemm_direct.h's kernel (six-bit codes, 128 x 256
+// tiles, two workgroups per compute unit): microseconds per chunk pair with the
+// compute unit full and with a workgroup alone on it (M = 2048, N = 8192 and
+// 4096, the slope between K = 2048 and 6144: W2A2 1.32 and 1.05, W4A4 1.92 and
+// 1.38), and a fixed part that grows with the output written at the end.
+double model_six_us(int M, int N, int K, int p, int cus) {
+  const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 255) / 256), pairs = (num_chunks(K) + 1) / 2;
+  const double pair = p <= 2 ? 1.32 : 1.92, alone = p <= 2 ? 1.05 : 1.38;
+  const int64_t full = tiles / (2 * cus), rem = tiles % (2 * cus);
+  return (double)pairs * (full * pair + (rem == 0 ? 0.0 : rem <= cus ? alone : pair)) +
+         2.5 + 0.025 * (double)std::min<int64_t>(tiles, 700);
+}
+
 double model_us(const Int8Shape& s, int f, int M, int N, int K, int grid, int cus) {
   return model_loop_us(s, f, M, N, K, grid, cus) + s.t[f].fixed_us;
 }
@@ -204,15 +219,15 @@ struct ShippedEntry {
 constexpr ShippedEntry kShipped[] = {
     { 4,   512,   512, 1, 2, {1, 0, 0, 0, 0, 0, 0, 0, 8, 0, 0, 0, 0, {0, 0, 0}}},  // w1a2_16x512x512
     {11, 11008,  4096, 4, 4, {3, 256, 128, 128, 4, 1, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w4a4_prefill_2048x11008x4096
-    { 9,  4096, 11008, 1, 1, {4, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w1a1_512x4096x11008
-    { 9,  4096, 11008, 1, 4, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w1a4_512x4096x11008
+    { 9,  4096, 11008, 1, 1, {1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w1a1_512x4096x11008 (few-token GEMM)
+    { 9,  4096, 11008, 1, 4, {1, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w1a4_512x4096x11008 (few-token GEMM)
     { 9,  4096, 11008, 2, 8, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w2a8_512x4096x11008
     { 9,  4096, 11008, 3, 3, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w3a3_512x4096x11008
     { 9,  4096, 11008, 3, 8, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w3a8_512x4096x11008
     { 9,  4096, 11008, 4, 8, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // sweep_w4a8_512x4096x11008
     {10,  4096,  4096, 2, 4, {3, 128, 128, 128, 2, 2, 0, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w2a4_q_m1024
-    {10, 11008,  4096, 2, 4, {3, 128, 128, 128, 2, 2, 512, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w2a4_gate_m1024
-    {10,  4096, 11008, 2, 4, {3, 128, 128, 128, 2, 2, 0, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w2a4_down_m1024
+    {10, 11008,  4096, 2, 4, {3, 256, 128, 128, 4, 1, 0, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w2a4_gate_m1024
+    {10,  4096, 11008, 2, 4, {3, 256, 128, 128, 4, 1, 0, 3, 0, 0, 0, 0, 0, {0, 0, 0}}},  // w2a4_down_m1024
 };
 
 // Approximate matching (Sec. V-B; the paper gives no distance): an entry
@@ -394,6 +409,10 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
     const int f = time_class(fp4, p);
     for (int i = 0; i < kNumInt8Shapes; ++i) {
       const Int8Shape& s = kInt8Shapes[i];
+      if (!fp4 && i == kSixShape && six_bit_ok(K, p, q)) {  // one workgroup per tile
+        consider(model_six_us(M, N, K, p, cus), i, 0, 0, -1);
+        continue;
+      }
       const int round = std::min(cus * s.per_cu, kMaxGrid);
       consider(model_us(s, f, M, N, K, 0, cus), i, 0, 0, -1);
       consider(model_us(s, f, M, N, K, round, cus), i, round, 0, -1);
@@ -420,9 +439,12 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
   // costs.  The MFMA figures were measured with every compute unit
   // busy and overstate grids of a few tiles by 10-40%, so they count at 90%
   // here (measured over M = 16..256, N, K = 1024..14336, p*q = 2..16).
+  // XOR + popcount itself only inside the range its model was fitted over
+  // (W1A1 1024 x 4096 x 4096, far outside, takes 266 us where 8 were modelled).
   const apt_config_t open = base_config(APT_ROUTE_XOR);
   const double few = thin_preferred(M, N, K, p, q, open, false) ? thin_us(M, N, K, p, q, false)
-                                                                : model_xor_us(M, N, K, p, q);
+                     : M <= 256 && (p * q >= 2 || (int64_t)M * N <= 32768) ? model_xor_us(M, N, K, p, q)
+                                                                           : HUGE_VAL;
   if (few < 0.9 * best) return open;
   const Int8Shape& s = kInt8Shapes[best_i];
   apt_config_t c = base_config(best_fp4 ? APT_ROUTE_FP4_MFMA : APT_ROUTE_INT8_MFMA);
