@@ -102,32 +102,34 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
 #pragma unroll
   for (int i = 0; i < kHeldIters; ++i)
     if (i < iters && word_of(i) < words) load(word_of(i), held[i]);
-  float rh = 0.0f, s2 = 0.0f;
+  Quantizer qz{};
   if constexpr (kHalf) {
     // Pass 1: the row's largest magnitude, then its scale.
-    ushort2_t mm = {0, 0};
+    HalfExtremes ex;
 #pragma unroll
     for (int i = 0; i < kHeldIters; ++i)
       if (i < iters && word_of(i) < words) {
-        mm = Src::fold_max(mm, held[i][0]);
-        mm = Src::fold_max(mm, held[i][1]);
+        ex.fold(held[i][0]);
+        ex.fold(held[i][1]);
       }
     for (int it = kHeldIters; it < iters; ++it) {
       const int w = word_of(it);
       if (w >= words) continue;
       uint32_t d[2][kD];
       load(w, d);
-      mm = Src::fold_max(mm, d[0]);
-      mm = Src::fold_max(mm, d[1]);
+      ex.fold(d[0]);
+      ex.fold(d[1]);
     }
-    uint32_t m = max((uint32_t)mm.x, (uint32_t)mm.y);
+    uint32_t m = ex.largest_magnitude();
     for (int off = kRows; off < kWave; off <<= 1) m = max(m, (uint32_t)__shfl_xor((int)m, off));
     if (wl == 0) lds_red[wave][r] = m;
     __syncthreads();
     m = 0u;
     for (int v = 0; v < nw; ++v) m = max(m, lds_red[v][r]);
     __syncthreads();  // lds_red is reused for the row sum
-    const uint16_t s16 = row_scale<B>(m, rh, s2);
+    qz.set(m, B);
+    const uint16_t s16 = qz.scale;
+    qz.quick = __ballot(!qz.quick) == 0ull;  // the form is the wave's, its lanes hold 8 rows
     if (wave == 0 && wl == 0 && real) {
       scale[row] = s16;
       if (scale_out != nullptr) scale_out[row] = s16;
@@ -139,8 +141,8 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
   uint32_t usum = 0u;
   auto emit = [&](int w, const uint32_t (&d)[2][kD]) __attribute__((always_inline)) {
     uint32_t c[8];  // byte b of c[i]: u of element 4 i + b of the word
-    Src::words(d[0], rh, s2, c);
-    Src::words(d[1], rh, s2, c + 4);
+    Src::words(d[0], qz, c);
+    Src::words(d[1], qz, c + 4);
     const int k0 = w * kWordElems;
 #pragma unroll
     for (int t = 0; t < 8; ++t) {  // padding elements and padding rows: u = 0

@@ -307,8 +307,13 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_thin_kernel(ThinParams 
     // straight into the operand's order
     auto convert_quick = [&](const rowcode::Quantizer& qz, int r) __attribute__((always_inline)) {
       uint32_t f[32], o[8], sum = 0u;
-      qz.quick_bits(held[r][0], f);
-      qz.quick_bits(held[r][1], f + 16);
+      if (C != kLow && q == 8) {
+        qz.quick_bits<true>(held[r][0], f);
+        qz.quick_bits<true>(held[r][1], f + 16);
+      } else {
+        qz.quick_bits<false>(held[r][0], f);
+        qz.quick_bits<false>(held[r][1], f + 16);
+      }
 #pragma unroll
       for (int t = 0; t < 8; ++t) {
         constexpr int kField[16] = {0, 6, 12, 18, 24, 30, 4, 10, 16, 22, 28, 2, 8, 14, 20, 26};
@@ -317,6 +322,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_thin_kernel(ThinParams 
         for (int i = 0; i < 4; ++i) e[i] = f[C == kLow ? kField[4 * (t % 4) + i] + t / 4 : 8 * i + t];
         o[t] = rowcode::Quantizer::gather(e);
         sum = __builtin_amdgcn_sad_u8(o[t], 0u, sum);
+        if (C != kLow && q == 8) o[t] ^= 0x80808080u;  // y = u - 128
       }
       usum += word_of(r) < words ? sum : 0u;
       store_word(word_of(r), o);
@@ -336,6 +342,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_thin_kernel(ThinParams 
       uint32_t v = 0u;
       for (int w = 0; w < wpr; ++w) v = max(v, s_max[src_row * wpr + w]);
       qz.set(v, q);
+      qz.quick = __builtin_amdgcn_readfirstlane(qz.quick);
       if (sub == 0 && lane == 0 && src_row < M) {
         s_rows[src_row] = __half2float(__ushort_as_half(qz.scale));
         if (prm.a_scale_out != nullptr && blockIdx.x == 0) prm.a_scale_out[src_row] = qz.scale;

@@ -213,8 +213,9 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
   load(wcur, 0);
   if (kB < T) load(wnxt, kB);
 
-  // fused fp16 source: each row's bipolar scale, and the quotient constants
-  __shared__ float s_row[SRC == kSrcHalf ? 3 * MT : 1];
+  // fused fp16 source: each row's bipolar scale, and its quantizer
+  __shared__ float s_row[SRC == kSrcHalf ? MT : 1];
+  __shared__ rowcode::Quantizer s_qz[SRC == kSrcHalf ? MT : 1];
   if (kALds && SRC == kSrcPacked) {
 #pragma unroll
     for (int k = 0; k < kStagePre; ++k) {
@@ -238,18 +239,17 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
 #pragma unroll
       for (int m = 0; m < kSrcRows; ++m) {
         if (m >= mrows) break;  // uniform
-        rowcode::ushort2_t mm = {0, 0};
+        rowcode::HalfExtremes ex;
 #pragma unroll
         for (int r = 0; r < kHeld; ++r)
-          if (r < src_rounds) mm = HalfSrc::fold_max(mm, sd[m][r]);
+          if (r < src_rounds) ex.fold(sd[m][r]);
         const __amdgpu_buffer_rsrc_t rs = s_rsrc(m);
         for (int r = kHeld; r < src_rounds; ++r) {
           uint32_t d[kSrcDwords];
           src_load(rs, r, d);
-          mm = HalfSrc::fold_max(mm, d);
+          ex.fold(d);
         }
-        uint32_t v = max((uint32_t)mm.x, (uint32_t)mm.y);
-        for (int off = kWave / 2; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
+        const uint32_t v = rowcode::wave_max(ex.largest_magnitude());
         if (lane == 0) s_red[m][wave] = v;
       }
       __syncthreads();
@@ -257,21 +257,20 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
         const int m = threadIdx.x;
         uint32_t v = 0u;
         for (int w = 0; w < nw; ++w) v = max(v, s_red[m][w]);
-        float rh, s2;
-        const uint16_t s16 = rowcode::row_scale<Q>(v, rh, s2);
-        s_row[3 * m] = __half2float(__ushort_as_half(s16));
-        s_row[3 * m + 1] = rh;
-        s_row[3 * m + 2] = s2;
-        if (prm.a_scale_out != nullptr && blockIdx.x == 0) prm.a_scale_out[m0 + m] = s16;
+        rowcode::Quantizer qz;
+        qz.set(v, Q);
+        s_qz[m] = qz;
+        s_row[m] = __half2float(__ushort_as_half(qz.scale));
+        if (prm.a_scale_out != nullptr && blockIdx.x == 0) prm.a_scale_out[m0 + m] = qz.scale;
       }
       __syncthreads();
     }
     const bool odd = (lane & 1) != 0;
     // uniform in r: both lanes of a pair run every round (DPP swap)
-    auto convert = [&](int m, int r, const uint32_t* d, float rh, float s2) __attribute__((always_inline)) {
+    auto convert = [&](int m, int r, const uint32_t* d, const rowcode::Quantizer& qz) __attribute__((always_inline)) {
       const int k0 = r * src_step + (int)threadIdx.x * rowcode::kLaneElems;
       uint32_t u[4];
-      if (SRC == kSrcHalf) HalfSrc::words(d, rh, s2, u); else CodeSrc::words(d, rh, s2, u);
+      if (SRC == kSrcHalf) HalfSrc::words(d, qz, u); else CodeSrc::words(d, qz, u);
 #pragma unroll
       for (int t = 0; t < 4; ++t) {  // elements past K: all-zero words
         const int n_valid = g.K - (k0 + 4 * t);
@@ -292,16 +291,20 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
 #pragma unroll
     for (int m = 0; m < kSrcRows; ++m) {
       if (m >= mrows) break;  // uniform
-      const float rh = SRC == kSrcHalf ? s_row[3 * m + 1] : 0.0f;
-      const float s2 = SRC == kSrcHalf ? s_row[3 * m + 2] : 0.0f;
+      rowcode::Quantizer qz{};
+      if (SRC == kSrcHalf) {
+        qz = s_qz[m];
+        qz.b = Q;
+        qz.quick = __builtin_amdgcn_readfirstlane(qz.quick);
+      }
 #pragma unroll
       for (int r = 0; r < kHeld; ++r)
-        if (r < src_rounds) convert(m, r, sd[m][r], rh, s2);
+        if (r < src_rounds) convert(m, r, sd[m][r], qz);
       const __amdgpu_buffer_rsrc_t rs = s_rsrc(m);
       for (int r = kHeld; r < src_rounds; ++r) {
         uint32_t d[kSrcDwords];
         src_load(rs, r, d);
-        convert(m, r, d, rh, s2);
+        convert(m, r, d, qz);
       }
     }
     __syncthreads();
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
       f = affine_value(c, __half2float(g.a_scale[mg]), sw, zw, (float)g.a_rowsum[mg],
                        __half2float(g.a_zero[mg]), sw * (float)g.w_rowsum[n] + (float)g.K * zw);
     } else {
-      f = (float)c * (SRC == kSrcHalf ? s_row[3 * m] : __half2float(g.a_scale[mg]));
+      f = (float)c * (SRC == kSrcHalf ? s_row[m] : __half2float(g.a_scale[mg]));
       f = f * __half2float(g.w_scale[n]);
     }
     g.c_fp16[o] = __float2half_rn(f);

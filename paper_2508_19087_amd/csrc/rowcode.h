@@ -7,7 +7,7 @@
 //
 // A lane takes 16 consecutive elements of a row.  CodeRow reads signed b-bit
 // codes (one byte each) and HalfRow fp16 values, which it quantizes with the
-// row's bipolar scale (see row_scale).  words() gives the 16 bipolar words u,
+// row's bipolar scale (see Quantizer).  words() gives the 16 bipolar words u,
 // one per byte; transpose8x8 leaves plane i of 8 elements in byte i; and
 // plane_word gives, for a pair of planes, the 32-bit plane word that this lane
 // and its neighbour (lanes 2m, 2m + 1, 32 consecutive elements) hold between
@@ -22,158 +22,7 @@ namespace rowcode {
 constexpr int kLaneElems = 16;
 constexpr uint32_t kRawBufferFlags = 0x00020000u;
 
-typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-
-// Signed b-bit codes, one byte each.
-template <bool kVec, int B>
-struct CodeRow {
-  static constexpr int kDwords = kLaneElems / 4;
-  static constexpr int kElemBytes = 1;
-  static constexpr bool kVector = kVec;
-  static constexpr bool kScaled = false;
-
-  // The lane's 16 codes from element k0 on.
-  __device__ static void load(__amdgpu_buffer_rsrc_t rsrc, int k0, uint32_t d[kDwords]) {
-    if (kVector) {
-      // K % 16 == 0: the lane's 16 codes are all in the row or all past it.
-      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (uint32_t)k0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) d[t] = v[t];
-    } else {
-#pragma unroll
-      for (int t = 0; t < kDwords; ++t) {
-        uint32_t w = 0u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          w |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rsrc, (uint32_t)(k0 + 4 * t + q), 0, 0)
-               << (8 * q);
-        d[t] = w;
-      }
-    }
-  }
-  // Bipolar words u = (x mod 2^b) XOR 2^(b-1), one per byte (Sec. III-A).
-  __device__ static void words(const uint32_t d[kDwords], float, float, uint32_t u[4]) {
-    constexpr uint32_t field = ((1u << B) - 1u) * 0x01010101u;
-    constexpr uint32_t flip = (1u << (B - 1)) * 0x01010101u;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) u[t] = (d[t] & field) ^ flip;
-  }
-};
-
-// fp16 activations, quantized with the row's scale.
-template <bool kVec, int B>
-struct HalfRow {
-  static constexpr int kDwords = kLaneElems / 2;
-  static constexpr int kElemBytes = 2;
-  static constexpr bool kVector = kVec;
-  static constexpr bool kScaled = true;
-
-  // The lane's 16 values from element k0 on (fp16 bits, two per dword).
-  __device__ static void load(__amdgpu_buffer_rsrc_t rsrc, int k0, uint32_t d[kDwords]) {
-    const uint32_t off = (uint32_t)k0 * 2u;
-    if (kVector) {
-      const u32x4_t v0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
-      const u32x4_t v1 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16u, 0, 0);
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        d[t] = v0[t];
-        d[4 + t] = v1[t];
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < kDwords; ++t) {
-        const uint32_t h0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off + 4u * t, 0, 0);
-        const uint32_t h1 = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off + 4u * t + 2u, 0, 0);
-        d[t] = (h0 & 0xFFFFu) | (h1 << 16);
-      }
-    }
-  }
-  // Largest |x| of the lane's values as fp16 bits, one maximum per 16-bit
-  // half: for finite values the order of |x| is the integer order of the bits
-  // without the sign.
-  __device__ static ushort2_t fold_max(ushort2_t m, const uint32_t d[kDwords]) {
-#pragma unroll
-    for (int t = 0; t < kDwords; ++t)
-      m = __builtin_elementwise_max(m, __builtin_bit_cast(ushort2_t, d[t] & 0x7FFF7FFFu));
-    return m;
-  }
-  // Bipolar words of the lane's 16 values, one per byte (element 4t + q in
-  // byte q of u[t]).  The signed code c = floor(h) clamped to the b-bit range
-  // goes into a byte as two's complement; the word is then
-  // (c mod 2^b) XOR 2^(b-1) = c + 2^(b-1), four bytes at once.  A zero's sign
-  // in h0 does not change floor(h).
-  __device__ static void words(const uint32_t d[kDwords], float rh, float s2, uint32_t u[4]) {
-#pragma clang fp contract(off)
-    constexpr int clo = -(1 << (B - 1)), chi = (1 << (B - 1)) - 1;
-    constexpr uint32_t field = ((1u << B) - 1u) * 0x01010101u;
-    constexpr uint32_t flip = (1u << (B - 1)) * 0x01010101u;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      uint32_t acc = 0u;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int j = 4 * t + q;
-        const uint32_t bits = (d[j / 2] >> (16 * (j % 2))) & 0xFFFFu;
-        const float x = __half2float(__ushort_as_half((unsigned short)bits));
-        const float h0 = __builtin_fmaf(x, rh, 0.0f);
-        const float e = __builtin_fmaf(-h0, s2, x);
-        const float h = __builtin_fmaf(e, rh, h0);  // RN(x / s) / 2
-        int c;  // floor(h) as int32 in one instruction (saturating)
-        asm("v_cvt_flr_i32_f32 %0, %1" : "=v"(c) : "v"(h));
-        c = min(max(c, clo), chi);
-        // byte q of acc <- low byte of c; the other bytes stay
-        const uint32_t sel = q == 1 ? 0x03020400u : q == 2 ? 0x03040100u : 0x04020100u;
-        acc = q == 0 ? (uint32_t)c : __builtin_amdgcn_perm((uint32_t)c, acc, sel);
-      }
-      u[t] = (acc & field) ^ flip;
-    }
-  }
-};
-
-// Delta swaps of an 8x8 bit-matrix transpose (bit 8r + c <-> bit 8c + r of a
-// 64-bit value, rows r = bytes): distance 7 and 14 stay inside each dword,
-// distance 28 moves nibbles between the dwords.  The three commute.
-__device__ __forceinline__ uint32_t swap7(uint32_t x) {
-  const uint32_t t = (x ^ (x >> 7)) & 0x00AA00AAu;
-  return x ^ t ^ (t << 7);
-}
-__device__ __forceinline__ uint32_t swap14(uint32_t x) {
-  const uint32_t t = (x ^ (x >> 14)) & 0x0000CCCCu;
-  return x ^ t ^ (t << 14);
-}
-
-// Transposes the bytes lo (rows 0..3) and hi (rows 4..7): afterwards bit j of
-// byte i is bit i of the former byte j.  With b <= 4 every byte is below 16:
-// the distance-28 swap just moves hi's low nibbles up into lo (hi becomes 0).
-template <int B>
-__device__ __forceinline__ void transpose8x8(uint32_t& lo, uint32_t& hi) {
-  if (B <= 4) {
-    lo = swap14(swap7(lo | (hi << 4)));
-    hi = 0u;
-  } else {
-    lo = swap14(swap7(lo));
-    hi = swap14(swap7(hi));
-    const uint32_t t = (lo ^ (hi << 4)) & 0xF0F0F0F0u;
-    lo ^= t;
-    hi ^= t >> 4;
-  }
-}
-
-// The rows' bipolar scale and the two constants of the exact half quotient
-// (HalfRow::words) from the largest magnitude's fp16 bits:
-// s = fp16(absmax / (2^B - 1)) with an IEEE fp32 divide, rh = RN(1 / s) / 2
-// (0 when s = 0, so that every quotient is 0), s2 = 2 s.  Returns the fp16 bits
-// of s.
-template <int B>
-__device__ __forceinline__ uint16_t row_scale(uint32_t absmax_bits, float& rh, float& s2) {
-  const float absmax = __half2float(__ushort_as_half((unsigned short)absmax_bits));
-  const __half s16 = __float2half_rn(__fdiv_rn(absmax, (float)((1 << B) - 1)));
-  const float s = __half2float(s16);
-  rh = s > 0.0f ? __fdiv_rn(1.0f, s) * 0.5f : 0.0f;
-  s2 = s * 2.0f;
-  return __half_as_ushort(s16);
-}
 
 // Largest value and sum over the wave's 64 lanes, uniform: four DPP steps give
 // every 16-lane row its result, four lane reads the wave's.
@@ -206,17 +55,20 @@ __device__ __forceinline__ void code_words(const uint32_t d[4], int b, uint32_t 
 // A row's quantizer: its scale from the largest magnitude's fp16 bits, and the
 // words of 16 of its values.
 //
-// Short form (b <= 7 and a normal scale): with h = x / (2 s), the word is
-// u = floor(h) + 2^(b-1), and no clamp is needed (|h| <= (2^b - 1)/2 (1 + 2^-11)).
-// One fma per value gives f = x / (2 s) + 2^(b-1) + 128 rounded to multiples of
-// 2^-16, whose bits 16..22 are u: the reciprocal's rounding moves h by at most
+// Short form (a normal scale): with h = x / (2 s), the word is u = floor(h) +
+// 2^(b-1), and no clamp is needed (|h| <= (2^b - 1)/2 (1 + 2^-11)).  One fma per
+// value gives f = x / (2 s) + 2^(b-1) + 128 rounded to multiples of 2^-16, whose
+// bits 16..22 are u (b = 8: + 256, multiples of 2^-15, bits 15..22): the reciprocal's rounding moves h by at most
 // 2^-18, so an integer h rounds back to itself, and h is never close below an
 // integer, since x and s have 11-bit significands: for |h| >= 1/2 a non-integer
 // h is at least 2^-12 away from every integer.  Negative
 // values above -s, where h comes arbitrarily close below 0, are first replaced
 // by -s (same word: h in [-1/2, 0)), as signed 16-bit integers, and -0 by +0.
-// The long form is the exact quotient of HalfRow::words; both give the same
-// words for every finite input (checked over all of them on the CPU).
+// The long form takes the exact quotient: h0 = fma(x, r / 2, 0), e = fma(-h0, 2 s,
+// x), h = fma(e, r / 2, h0) with r = RN(1 / s), the quotient correction of
+// Markstein's division with a correctly rounded reciprocal, floor and clamp.
+// Both give the same words for every finite input (checked over all of them on
+// the CPU).
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 // Largest and smallest of a lane's fp16 values (two dwords per packed
@@ -252,12 +104,13 @@ struct Quantizer {
     scale = __half_as_ushort(s16);
     rh = s > 0.0f ? __fdiv_rn(1.0f, s) * 0.5f : 0.0f;
     s2 = s * 2.0f;
-    quick = b <= 7 && scale >= 0x0400u;  // (uniform where the row is)
-    base = 128.0f + (float)(1 << (b - 1));
+    quick = scale >= 0x0400u;  // (uniform where the row is)
+    base = (float)((b == 8 ? 256 : 128) + (1 << (b - 1)));
     least = (0x8000u | scale) * 0x00010001u;
   }
 
-  // Short form: f[j], whose bits 16..22 are the word of value j.
+  // Short form: f[j], whose bits 16..23 are the word of value j.
+  template <bool kEight>  // b == 8
   __device__ __forceinline__ void quick_bits(const uint32_t d[8], uint32_t f[16]) const {
     typedef short short2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
@@ -265,13 +118,26 @@ struct Quantizer {
       const half2_t x0 = __builtin_bit_cast(half2_t, d[t]) + half2_t{(_Float16)0.0f, (_Float16)0.0f};
       const half2_t x = __builtin_bit_cast(
           half2_t, __builtin_elementwise_max(__builtin_bit_cast(short2_t, x0), __builtin_bit_cast(short2_t, least)));
-      f[2 * t] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.x, rh, base));
-      f[2 * t + 1] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.y, rh, base));
+      f[2 * t] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.x, rh, base)) << (kEight ? 1 : 0);
+      f[2 * t + 1] = __builtin_bit_cast(uint32_t, __builtin_fmaf((float)x.y, rh, base)) << (kEight ? 1 : 0);
     }
   }
-  // The words (bits 16..22) of four values in one dword.
+  // The words (bits 16..23) of four values in one dword.
   __device__ static __forceinline__ uint32_t gather(const uint32_t f[4]) {
     return __builtin_amdgcn_perm(f[1], f[0], 0x0C0C0602u) | __builtin_amdgcn_perm(f[3], f[2], 0x06020C0Cu);
+  }
+
+  // The 16 words of a lane, element 4 t + i in byte i of u[t].
+  __device__ __forceinline__ void words(const uint32_t d[8], uint32_t u[4]) const {
+    if (quick) {
+      uint32_t f[16];
+      if (b == 8) quick_bits<true>(d, f);
+      else quick_bits<false>(d, f);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) u[t] = gather(f + 4 * t);
+    } else {
+      exact_words(d, u);
+    }
   }
 
   __device__ __forceinline__ void exact_words(const uint32_t d[8], uint32_t u[4]) const {
@@ -300,6 +166,102 @@ struct Quantizer {
     }
   }
 };
+
+// Signed b-bit codes, one byte each.
+template <bool kVec, int B>
+struct CodeRow {
+  static constexpr int kDwords = kLaneElems / 4;
+  static constexpr int kElemBytes = 1;
+  static constexpr bool kVector = kVec;
+  static constexpr bool kScaled = false;
+
+  // The lane's 16 codes from element k0 on.
+  __device__ static void load(__amdgpu_buffer_rsrc_t rsrc, int k0, uint32_t d[kDwords]) {
+    if (kVector) {
+      // K % 16 == 0: the lane's 16 codes are all in the row or all past it.
+      const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (uint32_t)k0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) d[t] = v[t];
+    } else {
+#pragma unroll
+      for (int t = 0; t < kDwords; ++t) {
+        uint32_t w = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          w |= (uint32_t)__builtin_amdgcn_raw_buffer_load_b8(rsrc, (uint32_t)(k0 + 4 * t + q), 0, 0)
+               << (8 * q);
+        d[t] = w;
+      }
+    }
+  }
+  // Bipolar words u = (x mod 2^b) XOR 2^(b-1), one per byte (Sec. III-A).
+  __device__ static void words(const uint32_t d[kDwords], const Quantizer&, uint32_t u[4]) {
+    constexpr uint32_t field = ((1u << B) - 1u) * 0x01010101u;
+    constexpr uint32_t flip = (1u << (B - 1)) * 0x01010101u;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) u[t] = (d[t] & field) ^ flip;
+  }
+};
+
+// fp16 activations, quantized with the row's scale.
+template <bool kVec, int B>
+struct HalfRow {
+  static constexpr int kDwords = kLaneElems / 2;
+  static constexpr int kElemBytes = 2;
+  static constexpr bool kVector = kVec;
+  static constexpr bool kScaled = true;
+
+  // The lane's 16 values from element k0 on (fp16 bits, two per dword).
+  __device__ static void load(__amdgpu_buffer_rsrc_t rsrc, int k0, uint32_t d[kDwords]) {
+    const uint32_t off = (uint32_t)k0 * 2u;
+    if (kVector) {
+      const u32x4_t v0 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+      const u32x4_t v1 = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16u, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        d[t] = v0[t];
+        d[4 + t] = v1[t];
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < kDwords; ++t) {
+        const uint32_t h0 = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off + 4u * t, 0, 0);
+        const uint32_t h1 = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off + 4u * t + 2u, 0, 0);
+        d[t] = (h0 & 0xFFFFu) | (h1 << 16);
+      }
+    }
+  }
+  __device__ static void words(const uint32_t d[kDwords], const Quantizer& qz, uint32_t u[4]) { qz.words(d, u); }
+};
+
+// Delta swaps of an 8x8 bit-matrix transpose (bit 8r + c <-> bit 8c + r of a
+// 64-bit value, rows r = bytes): distance 7 and 14 stay inside each dword,
+// distance 28 moves nibbles between the dwords.  The three commute.
+__device__ __forceinline__ uint32_t swap7(uint32_t x) {
+  const uint32_t t = (x ^ (x >> 7)) & 0x00AA00AAu;
+  return x ^ t ^ (t << 7);
+}
+__device__ __forceinline__ uint32_t swap14(uint32_t x) {
+  const uint32_t t = (x ^ (x >> 14)) & 0x0000CCCCu;
+  return x ^ t ^ (t << 14);
+}
+
+// Transposes the bytes lo (rows 0..3) and hi (rows 4..7): afterwards bit j of
+// byte i is bit i of the former byte j.  With b <= 4 every byte is below 16:
+// the distance-28 swap just moves hi's low nibbles up into lo (hi becomes 0).
+template <int B>
+__device__ __forceinline__ void transpose8x8(uint32_t& lo, uint32_t& hi) {
+  if (B <= 4) {
+    lo = swap14(swap7(lo | (hi << 4)));
+    hi = 0u;
+  } else {
+    lo = swap14(swap7(lo));
+    hi = swap14(swap7(hi));
+    const uint32_t t = (lo ^ (hi << 4)) & 0xF0F0F0F0u;
+    lo ^= t;
+    hi ^= t >> 4;
+  }
+}
 
 // This lane's word of plane pair (i, i + 1) after transpose8x8 of its two
 // 8-element groups (lo/hi of elements 0..7 in sa, of 8..15 in sb): the even

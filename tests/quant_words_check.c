@@ -1,8 +1,9 @@
 /* Checks the kernels' short form of the fp16 quantizer over every input it
- * takes: for every width b = 1..7, every largest magnitude A of a row (positive
+ * takes: for every width b = 1..8, every largest magnitude A of a row (positive
  * finite fp16 bits) whose scale s = fp16(A / (2^b - 1)) is normal, and every
  * fp16 x with |x| <= A (both zeros), the word from one fma,
- *   u = bits 16..22 of fma(x', 1 / (2 s), 128 + 2^(b-1)),
+ *   u = bits 16..22 of fma(x', 1 / (2 s), 128 + 2^(b-1)) for b <= 7,
+ *   u = bits 15..22 of fma(x', 1 / (2 s), 256 + 128) for b = 8,
  *   x' = x, with values in [-s, 0) replaced by -s and -0 by +0,
  * must equal 2^(b-1) + floor(x / (2 s)), the quotient taken in float64.
  * Prints "tested <count>" and exits 0, or prints the first failure and exits 1.
@@ -35,11 +36,11 @@ int main(int argc, char** argv) {
   for (uint32_t h = 0; h < 0x7C00u; ++h) value[h] = half_value(h);
   long long tested = 0;
   int failed = 0;
-  for (int b = 1; b <= 7; ++b) {
+  for (int b = 1; b <= 8; ++b) {
     static uint32_t top[32768]; /* largest A of each scale */
     memset(top, 0, sizeof top);
     for (uint32_t A = 1; A < 0x7C00u; ++A) top[half_bits(value[A] / (float)((1 << b) - 1))] = A;
-    const float base = 128.0f + (float)(1 << (b - 1));
+    const float base = (b == 8 ? 256.0f : 128.0f) + (float)(1 << (b - 1));
 #pragma omp parallel for schedule(dynamic, 64) reduction(+ : tested) reduction(| : failed)
     for (uint32_t sb = 0x0400u; sb < 0x7C00u; ++sb) {
       if (top[sb] == 0) continue;
@@ -57,7 +58,7 @@ int main(int argc, char** argv) {
           int want = (int)floor((double)x * inv);
           while ((double)want * 2.0 * (double)s > (double)x) --want;
           while ((double)(want + 1) * 2.0 * (double)s <= (double)x) ++want;
-          bad |= (int)((bits >> 16) & 0xFFu) != want + (1 << (b - 1));
+          bad |= (int)((bits >> (b == 8 ? 15 : 16)) & 0xFFu) != want + (1 << (b - 1));
         }
       }
       tested += 2ll * (top[sb] + 1);
