@@ -78,6 +78,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
       const_cast<uint8_t*>(src), 0, (uint32_t)((int64_t)M * K * Src::kElemBytes), kRawBufferFlags);
   const int64_t row_off = (int64_t)row * K;  // elements
+  const uint8_t* const row_src = src + (real ? row_off : 0) * Src::kElemBytes;
   auto word_of = [&](int it) { return it * step + wave * kWordLanes + wl; };
   // the 32 elements of word w of this lane's row, elements past K as zero bits
   auto load = [&](int w, uint32_t (&d)[2][kD]) __attribute__((always_inline)) {
@@ -86,7 +87,9 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(
     for (int h = 0; h < 2; ++h) {
       const int kh = k0 + h * kLaneElems;
       // (whole-source byte offsets stay below 2^31: the host checks)
-      Src::load(rsrc, (int)(row_off + (kh < K ? kh : 0)), d[h]);
+      // (rows at any byte: whole groups are one unaligned load each)
+      if (!kVec && real && kh + kLaneElems <= K) Src::wide(row_src + (int64_t)kh * Src::kElemBytes, d[h]);
+      else Src::load(rsrc, (int)(row_off + (kh < K ? kh : 0)), d[h]);
       const int n_valid = real ? K - kh : 0;
 #pragma unroll
       for (int t = 0; t < kD; ++t) {

@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
   const int q = g.q;
   const uint32_t ca = (uint32_t)(1 - (1 << q)), cw = (uint32_t)int8::offset_of(P);
   const uint32_t const_term = ca * cw * (uint32_t)g.K;  // (padding words are 0 and add nothing)
-  const bool fp16 = g.c_fp16 != nullptr, affine = g.a_zero != nullptr, vec_ok = prm.vec_out != 0;
+  const bool fp16 = g.c_fp16 != nullptr, affine = g.a_zero != nullptr;
   uint32_t* const s_term = reinterpret_cast<uint32_t*>(stage1);       // columns, then rows
   float* const s_scale = reinterpret_cast<float*>(s_term + kBN + kBM);
   float* const s_zero = s_scale + kBN + kBM;                          // z_w[n] | float(R_a[m])
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
       __builtin_amdgcn_s_waitcnt(0xc07f);  // this wave's LDS writes are done
       __builtin_amdgcn_wave_barrier();
       const int nl = wave * 64 + b * 32 + ec, ncol = n0 + nl;
-      const bool full = vec_ok && ncol + 3 < g.N;
+      const bool full = ncol + 3 < g.N;
       const v4u wt = *reinterpret_cast<const v4u*>(s_term + nl);
       const v4f ws = *reinterpret_cast<const v4f*>(s_scale + nl);
       v4i dv[4];
@@ -350,7 +350,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
               hb[j / 2] = __half_as_ushort(__float2half_rn(f[j])) |
                           ((uint32_t)__half_as_ushort(__float2half_rn(f[j + 1])) << 16);
             if (full)
-              *reinterpret_cast<uint2*>(g.c_fp16 + o) = make_uint2(hb[0], hb[1]);
+              int8::store8(g.c_fp16 + o, hb[0], hb[1]);
             else
               for (int j = 0; j < 4 && ncol + j < g.N; ++j)
                 g.c_fp16[o + j] = __ushort_as_half((unsigned short)(hb[j / 2] >> (16 * (j % 2))));

@@ -104,10 +104,17 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // One 16-byte streaming global store of output bytes (written once, not
-// re-read).  As a plain store the compiler shares the first element's store
-// with the element-wise edge path and splits the vector into 12 + 4 bytes.
+// re-read), at any int32.  As a plain store the compiler shares the first
+// element's store with the element-wise edge path and splits the vector into
+// 12 + 4 bytes.
+typedef int any_v4i __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ void store16(int32_t* p, v4i v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<v4i*>(p));
+  __builtin_nontemporal_store(v, reinterpret_cast<any_v4i*>(p));
+}
+// Four halves at any half.
+typedef uint32_t any_v2u __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ void store8(__half* p, uint32_t lo, uint32_t hi) {
+  *reinterpret_cast<any_v2u*>(p) = any_v2u{lo, hi};
 }
 
 // An empty instruction that reads x: code computing x cannot be moved past it.
@@ -138,7 +145,6 @@ struct Int8Params {
   v4i* partial;       // stream-K: two partial tiles per workgroup (workspace)
   uint32_t partial_bytes;
   int* counters;      // stream-K: arrivals per stream-K tile (workspace, zeroed per call)
-  int vec_out;        // outputs take 16-byte (int32) / 8-byte (fp16) row stores
 };
 
 // Bytes of the activation fragment buffer for M rows and K in operand format
@@ -682,7 +688,6 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
         : 4u * (uint32_t)(NC * kChunk - g.K) * (uint32_t)((q == 8 ? -128 : 0) * pad_of(P));
   const uint32_t const_term = ca * cw * (uint32_t)g.K + pad_term;
   const bool fp16 = g.c_fp16 != nullptr;
-  const bool vec_ok = prm.vec_out != 0;
 
   // Epilogue terms of tile (m0, n0): one value per thread, fetched a pair of
   // chunks before the tile's flush and written to LDS before that pair's
@@ -793,7 +798,7 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
         __builtin_amdgcn_wave_barrier();
         const int nl = wn * WTN + b * 32 + ec;  // column in the tile
         const int ncol = n0 + nl;
-        const bool full = vec_ok && ncol + 3 < g.N;
+        const bool full = ncol + 3 < g.N;
         const v4u wt = *reinterpret_cast<const v4u*>(lds_wt + nl);
         const v4f ws = *reinterpret_cast<const v4f*>(lds_ws + nl);
         // the block's four rows and their row terms are read together, before
@@ -846,7 +851,7 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
                 hb[j / 2] = h0 | (h1 << 16);
               }
               if (full)
-                *reinterpret_cast<uint2*>(g.c_fp16 + o) = make_uint2(hb[0], hb[1]);
+                store8(g.c_fp16 + o, hb[0], hb[1]);
               else
                 for (int j = 0; j < 4 && ncol + j < g.N; ++j)
                   g.c_fp16[o + j] = __ushort_as_half((unsigned short)(hb[j / 2] >> (16 * (j % 2))));

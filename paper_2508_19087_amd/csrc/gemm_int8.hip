@@ -221,8 +221,6 @@ hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* wo
     p.dp_tiles = pl[i].dp_tiles;
     p.sk_pairs = pl[i].sk_pairs;
     p.sk_grid = pl[i].sk_grid;
-    p.vec_out = g.N % 4 == 0 && (reinterpret_cast<uintptr_t>(g.c_int32) & 15) == 0 &&
-                (reinterpret_cast<uintptr_t>(g.c_fp16) & 7) == 0;
     p.partial_bytes = (uint32_t)pl[i].partial_bytes;
   }
   // Counters of all launches first (one clearing pass), then partial tiles.

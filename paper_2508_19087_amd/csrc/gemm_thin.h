@@ -190,19 +190,19 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_thin_kernel(ThinParams 
   using Half = std::integral_constant<bool, true>;
   using Code = std::integral_constant<bool, false>;
   const int src_bytes = prm.src == kSrcHalf ? 2 : 1;
-  const __amdgpu_buffer_rsrc_t s_rsrc =
-      rsrc_of(static_cast<const uint8_t*>(prm.a_src) + (int64_t)(src_row < M ? src_row : 0) * g.K * src_bytes,
-              (uint32_t)g.K * src_bytes);
+  const uint8_t* const src_base =
+      static_cast<const uint8_t*>(prm.a_src) + (int64_t)(src_row < M ? src_row : 0) * g.K * src_bytes;
+  const __amdgpu_buffer_rsrc_t s_rsrc = rsrc_of(src_base, (uint32_t)g.K * src_bytes);
   auto load_word = [&](auto half, int r, uint32_t (&d)[2][8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int k0 = word_of(r) * 32 + h * rowcode::kLaneElems;
       if constexpr (half.value) {
         if (prm.a_vec) rowcode::HalfRow<true, 8>::load(s_rsrc, k0, d[h]);
-        else rowcode::HalfRow<false, 8>::load(s_rsrc, k0, d[h]);
+        else rowcode::HalfRow<false, 8>::load_row(s_rsrc, src_base, g.K, k0, d[h]);
       } else {
         if (prm.a_vec) rowcode::CodeRow<true, 8>::load(s_rsrc, k0, d[h]);
-        else rowcode::CodeRow<false, 8>::load(s_rsrc, k0, d[h]);
+        else rowcode::CodeRow<false, 8>::load_row(s_rsrc, src_base, g.K, k0, d[h]);
       }
     }
   };

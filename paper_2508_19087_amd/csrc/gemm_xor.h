@@ -168,12 +168,13 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
     return xor_rsrc(static_cast<const uint8_t*>(prm.a_src) + (int64_t)(m0 + m) * g.K * kElemBytes,
                     (uint32_t)g.K * kElemBytes);
   };
-  auto src_load = [&](__amdgpu_buffer_rsrc_t rs, int r, uint32_t* d) __attribute__((always_inline)) {
+  auto src_load = [&](__amdgpu_buffer_rsrc_t rs, int m, int r, uint32_t* d) __attribute__((always_inline)) {
     const int k0 = r * src_step + (int)threadIdx.x * rowcode::kLaneElems;
+    const uint8_t* const row = static_cast<const uint8_t*>(prm.a_src) + (int64_t)(m0 + m) * g.K * kElemBytes;
     if (SRC == kSrcHalf) {
-      if (prm.a_vec) HalfVec::load(rs, k0, d); else HalfSrc::load(rs, k0, d);
+      if (prm.a_vec) HalfVec::load(rs, k0, d); else HalfSrc::load_row(rs, row, g.K, k0, d);
     } else {
-      if (prm.a_vec) CodeVec::load(rs, k0, d); else CodeSrc::load(rs, k0, d);
+      if (prm.a_vec) CodeVec::load(rs, k0, d); else CodeSrc::load_row(rs, row, g.K, k0, d);
     }
   };
   uint32_t sd[kSrcRows][kHeld][kSrcDwords];
@@ -184,7 +185,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
       const __amdgpu_buffer_rsrc_t rs = s_rsrc(m);
 #pragma unroll
       for (int r = 0; r < kHeld; ++r)
-        if (r < src_rounds) src_load(rs, r, sd[m][r]);
+        if (r < src_rounds) src_load(rs, m, r, sd[m][r]);
     }
   }
 
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
         const __amdgpu_buffer_rsrc_t rs = s_rsrc(m);
         for (int r = kHeld; r < src_rounds; ++r) {
           uint32_t d[kSrcDwords];
-          src_load(rs, r, d);
+          src_load(rs, m, r, d);
           ex.fold(d);
         }
         const uint32_t v = rowcode::wave_max(ex.largest_magnitude());
@@ -303,7 +304,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
       const __amdgpu_buffer_rsrc_t rs = s_rsrc(m);
       for (int r = kHeld; r < src_rounds; ++r) {
         uint32_t d[kSrcDwords];
-        src_load(rs, r, d);
+        src_load(rs, m, r, d);
         convert(m, r, d, qz);
       }
     }

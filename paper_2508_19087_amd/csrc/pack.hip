@@ -73,8 +73,9 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void pack_rows_kernel(
   const int pad_rows = row == rows - 1 ? (rows + kRowGroup - 1) / kRowGroup * kRowGroup - rows : 0;
   const int kpad = nchunks * kChunk;
   const int nsteps = (kpad + kStep - 1) / kStep;
+  const uint8_t* const row_src = src + (int64_t)row * K * Src::kElemBytes;
   const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint8_t*>(src + (int64_t)row * K * Src::kElemBytes), 0,
+      const_cast<uint8_t*>(row_src), 0,
       (uint32_t)K * Src::kElemBytes, kRawBufferFlags);
   auto k_of = [&](int j) { return j * kStep + lane * kLaneElems; };
 
@@ -85,7 +86,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void pack_rows_kernel(
     HalfExtremes ex;
     for (int j0 = wave; j0 < nsteps; j0 += kHeld * nw) {
 #pragma unroll
-      for (int t = 0; t < kHeld; ++t) Src::load(rsrc, k_of(j0 + t * nw), d[t]);
+      for (int t = 0; t < kHeld; ++t) Src::load_row(rsrc, row_src, K, k_of(j0 + t * nw), d[t]);
 #pragma unroll
       for (int t = 0; t < kHeld; ++t) ex.fold(d[t]);
       if (kSteps > 0) break;  // one round covers all steps; d stays for pass 2
@@ -100,7 +101,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void pack_rows_kernel(
     if (threadIdx.x == 0) scale[row] = qz.scale;
   } else if (kSteps > 0) {
 #pragma unroll
-    for (int t = 0; t < kHeld; ++t) Src::load(rsrc, k_of(wave + t * nw), d[t]);
+    for (int t = 0; t < kHeld; ++t) Src::load_row(rsrc, row_src, K, k_of(wave + t * nw), d[t]);
   }
 
   // Pass 2: convert (or quantize) and pack.
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void pack_rows_kernel(
   } else {
     for (int j0 = wave; j0 < nsteps; j0 += kHeld * nw) {
 #pragma unroll
-      for (int t = 0; t < kHeld; ++t) Src::load(rsrc, k_of(j0 + t * nw), d[t]);
+      for (int t = 0; t < kHeld; ++t) Src::load_row(rsrc, row_src, K, k_of(j0 + t * nw), d[t]);
 #pragma unroll
       for (int t = 0; t < kHeld; ++t)
         if (j0 + t * nw < nsteps) process(j0 + t * nw, d[t]);

@@ -23,6 +23,7 @@ constexpr int kLaneElems = 16;
 constexpr uint32_t kRawBufferFlags = 0x00020000u;
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+typedef uint32_t any_u32x4_t __attribute__((ext_vector_type(4), aligned(1)));  // at any byte
 
 // Largest value and sum over the wave's 64 lanes, uniform: four DPP steps give
 // every 16-lane row its result, four lane reads the wave's.
@@ -194,6 +195,29 @@ struct CodeRow {
       }
     }
   }
+  // 16 codes at any byte.
+  __device__ static void wide(const uint8_t* p, uint32_t d[kDwords]) {
+    const any_u32x4_t v = *reinterpret_cast<const any_u32x4_t*>(p);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) d[t] = v[t];
+  }
+  // The same from a row of K codes at `row`: where rows start at any byte, whole
+  // groups are one unaligned 16-byte load and only the group across the row's end
+  // takes byte loads.  W3A8 333 x 5003 x 2999 from codes, the GEMM's row stores at
+  // any alignment included: 30.3 us with 16 byte loads per group and single
+  // stores, 25.9 us so.
+  __device__ static void load_row(__amdgpu_buffer_rsrc_t rsrc, const uint8_t* row, int K, int k0, uint32_t d[kDwords]) {
+    if (kVector) {
+      load(rsrc, k0, d);
+    } else if (k0 + kLaneElems <= K) {
+      wide(row + k0, d);
+    } else if (k0 < K) {
+      load(rsrc, k0, d);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) d[t] = 0u;
+    }
+  }
   // Bipolar words u = (x mod 2^b) XOR 2^(b-1), one per byte (Sec. III-A).
   __device__ static void words(const uint32_t d[kDwords], const Quantizer&, uint32_t u[4]) {
     constexpr uint32_t field = ((1u << B) - 1u) * 0x01010101u;
@@ -229,6 +253,27 @@ struct HalfRow {
         const uint32_t h1 = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off + 4u * t + 2u, 0, 0);
         d[t] = (h0 & 0xFFFFu) | (h1 << 16);
       }
+    }
+  }
+  // As CodeRow's.
+  __device__ static void wide(const uint8_t* p, uint32_t d[kDwords]) {
+    const any_u32x4_t v0 = reinterpret_cast<const any_u32x4_t*>(p)[0], v1 = reinterpret_cast<const any_u32x4_t*>(p)[1];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      d[t] = v0[t];
+      d[4 + t] = v1[t];
+    }
+  }
+  __device__ static void load_row(__amdgpu_buffer_rsrc_t rsrc, const uint8_t* row, int K, int k0, uint32_t d[kDwords]) {
+    if (kVector) {
+      load(rsrc, k0, d);
+    } else if (k0 + kLaneElems <= K) {
+      wide(row + (int64_t)k0 * 2, d);
+    } else if (k0 < K) {
+      load(rsrc, k0, d);
+    } else {
+#pragma unroll
+      for (int t = 0; t < 8; ++t) d[t] = 0u;
     }
   }
   __device__ static void words(const uint32_t d[kDwords], const Quantizer& qz, uint32_t u[4]) { qz.words(d, u); }
