@@ -69,7 +69,8 @@ __device__ __forceinline__ void code_words(const uint32_t d[4], int b, uint32_t 
 // x), h = fma(e, r / 2, h0) with r = RN(1 / s), the quotient correction of
 // Markstein's division with a correctly rounded reciprocal, floor and clamp.
 // Both give the same words for every finite input (checked over all of them on
-// the CPU).
+// the CPU); a row with an infinity or a NaN takes the long form, whose words stay
+// in range.
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
 // Largest and smallest of a lane's fp16 values (two dwords per packed
@@ -105,7 +106,7 @@ struct Quantizer {
     scale = __half_as_ushort(s16);
     rh = s > 0.0f ? __fdiv_rn(1.0f, s) * 0.5f : 0.0f;
     s2 = s * 2.0f;
-    quick = scale >= 0x0400u;  // (uniform where the row is)
+    quick = scale - 0x0400u < 0x7800u;  // normal and finite (uniform where the row is)
     base = (float)((b == 8 ? 256 : 128) + (1 << (b - 1)));
     least = (0x8000u | scale) * 0x00010001u;
   }

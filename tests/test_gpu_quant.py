@@ -123,3 +123,19 @@ def test_quantized_activations_through_gemm(M, N, K, p, q):
     E, _ = ref.epilogue(C, s16, w_scale)
     assert ref.fp16_close(c16.cpu().numpy(), E).all()
     assert np.array_equal(a_scale.cpu().numpy().view(np.uint16), s16.view(np.uint16))
+
+
+@pytest.mark.parametrize("q", [1, 4, 7, 8])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+def test_rows_with_a_value_that_is_not_finite_keep_words_in_range(q, bad):
+    """The codes of such a row are unspecified, but its planes and row sum
+    describe the same codes, and the rows beside it are as without it."""
+    K = 1040
+    x = synth.fp16_activations(synth.rng(73, q), 3, K)
+    x[1, 700] = bad
+    words, rs, sc = gpu_quant(x, q)
+    u, _ = ref.unpack(words, 3, K, q)
+    assert np.array_equal(rs, ref.rowsum(ref.decode(u, q)))
+    for m in (0, 2):
+        w, wr, ws, codes = expected(x[m:m + 1], q)
+        assert rs[m] == wr[0] and sc[m] == ws[0] and np.array_equal(u[m], ref.convert(codes, q)[0])
