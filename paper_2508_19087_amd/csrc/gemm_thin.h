@@ -1,4 +1,4 @@
-// gemm_thin.h - the few-token GEMM (M <= 128) of the WpAq bipolar-INT path on
+// gemm_thin.h - the few-token GEMM (M <= 512) of the WpAq bipolar-INT path on
 // the matrix cores of gfx950 (APT-LLM, arXiv 2508.19087, Sec. III-B): the
 // packed weights are streamed once, rebuilt from their bit-planes in
 // registers and multiplied with activations that stay in registers.
