@@ -65,6 +65,8 @@ constexpr int kNumMainShapes = 3;
 constexpr int kFirstTail = 2;
 // The shape that runs on six-bit codes where they hold the operands (gemm_direct.h).
 constexpr int kSixShape = 2;
+// The shape with figures of its own in a round that is not full (tall_round).
+constexpr int kTallShape = 1;
 // Device-wide rate at which stream-K partial tiles are written and read back
 // (bytes per microsecond), as the stream-K launches measured on MI355X show.
 constexpr double kPartialBytesPerUs = 2.5e6;
@@ -160,6 +162,19 @@ double model_six_us(int M, int N, int K, int p, int cus) {
   return (double)pairs * (full * pair + (rem == 0 ? 0.0 : rem <= cus ? alone : pair)) +
          2.5 + 0.025 * (double)std::min<int64_t>(tiles, 700);
 }
+
+// Weights of 7 and 8 bits on the 512 x 128 shape in one round that leaves
+// compute units over: a chunk pair takes 3.1 to 3.4 us there, against 4.04 with
+// all of them busy (W8A8, 64 to 192 tiles), so the shape's figures, taken over a
+// full round, overstate it (1024 x 12288 x 4096 95 us modelled, 70 measured
+// against 75 on 128 x 128 tiles).  Only where N has no partial tile: with one the
+// shape measured up to 16% slower than the others (997 x 12234 x 1506 58.7
+// against 49.1 us).  The figures are 10% above the measured ones, since nearer than
+// that the other shapes are as good (1778 x 4736 x 1408 36.0 against 34.7).
+bool tall_round(int M, int N, int p, int cus) {
+  return p >= 7 && N % 128 == 0 && (int64_t)((M + 511) / 512) * (N / 128) < cus;
+}
+double model_tall_us(int K) { return 1.10 * (((num_chunks(K) + 1) / 2) * 3.3 + 17.5); }
 
 double model_us(const Int8Shape& s, int f, int M, int N, int K, int grid, int cus) {
   return model_loop_us(s, f, M, N, K, grid, cus) + s.t[f].fixed_us;
@@ -414,7 +429,7 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
         continue;
       }
       const int round = std::min(cus * s.per_cu, kMaxGrid);
-      consider(model_us(s, f, M, N, K, 0, cus), i, 0, 0, -1);
+      consider(!fp4 && i == kTallShape && tall_round(M, N, p, cus) ? model_tall_us(K) : model_us(s, f, M, N, K, 0, cus), i, 0, 0, -1);
       consider(model_us(s, f, M, N, K, round, cus), i, round, 0, -1);
     }
     for (int i = 0; i < kNumMainShapes; ++i) {
