@@ -42,7 +42,7 @@ namespace direct {
 using int8::Int8Params;
 using int8::keep_here;
 using int8::make_rsrc;
-using int8::store16;
+using int8::store_block;
 using int8::v16f;
 using int8::v16i;
 using int8::v2i;
@@ -213,7 +213,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
   const int q = g.q;
   const uint32_t ca = (uint32_t)(1 - (1 << q)), cw = (uint32_t)int8::offset_of(P);
   const uint32_t const_term = ca * cw * (uint32_t)g.K;  // (padding words are 0 and add nothing)
-  const bool fp16 = g.c_fp16 != nullptr, affine = g.a_zero != nullptr;
+  const bool fp16 = g.c_fp16 != nullptr, affine = g.a_zero != nullptr, stream = prm.stream_out != 0;
   uint32_t* const s_term = reinterpret_cast<uint32_t*>(stage1);       // columns, then rows
   float* const s_scale = reinterpret_cast<float*>(s_term + kBN + kBM);
   float* const s_zero = s_scale + kBN + kBM;                          // z_w[n] | float(R_a[m])
@@ -305,7 +305,6 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
       __builtin_amdgcn_s_waitcnt(0xc07f);  // this wave's LDS writes are done
       __builtin_amdgcn_wave_barrier();
       const int nl = wave * 64 + b * 32 + ec, ncol = n0 + nl;
-      const bool full = ncol + 3 < g.N;
       const v4u wt = *reinterpret_cast<const v4u*>(s_term + nl);
       const v4f ws = *reinterpret_cast<const v4f*>(s_scale + nl);
       v4i dv[4];
@@ -317,45 +316,37 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) keep_here(dv[i], atv[i]);
+      int32_t cv[4][4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int ml = a * 32 + er + 8 * i, m = m0 + ml;
-        int32_t cv[4];
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) cv[j] = (int32_t)(4u * (uint32_t)dv[i][j] + atv[i] + wt[j]);
-        if (m < g.M && ncol < g.N) {
-          const int64_t o = (int64_t)m * g.N + ncol;
-          if (g.c_int32) {
-            if (full)
-              store16(g.c_int32 + o, v4i{cv[0], cv[1], cv[2], cv[3]});
-            else
-              for (int j = 0; j < 4 && ncol + j < g.N; ++j) g.c_int32[o + j] = cv[j];
+        for (int j = 0; j < 4; ++j) cv[i][j] = (int32_t)(4u * (uint32_t)dv[i][j] + atv[i] + wt[j]);
+      const int row0 = a * 32 + er;
+      const bool inside = m0 + a * 32 + 32 <= g.M && n0 + wave * 64 + b * 32 + 32 <= g.N;
+      if (g.c_int32 != nullptr) store_block(g, cv, m0 + row0, ncol, inside, stream);
+      if (fp16) {
+        uint32_t hb[4][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int ml = row0 + 8 * i;
+          const float sa = s_scale[kBN + ml];
+          float f[4];
+          if (affine) {
+            const v4f zw = *reinterpret_cast<const v4f*>(s_zero + nl);
+            const v4f col = *reinterpret_cast<const v4f*>(s_cross + nl);
+            const float ra = s_zero[kBN + ml], za = s_cross[kBN + ml];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = affine_value(cv[i][j], sa, ws[j], zw[j], ra, za, col[j]);
+          } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) f[j] = (float)cv[i][j] * sa * ws[j];
           }
-          if (fp16) {
-            const float sa = s_scale[kBN + ml];
-            float f[4];
-            if (affine) {
-              const v4f zw = *reinterpret_cast<const v4f*>(s_zero + nl);
-              const v4f col = *reinterpret_cast<const v4f*>(s_cross + nl);
-              const float ra = s_zero[kBN + ml], za = s_cross[kBN + ml];
 #pragma unroll
-              for (int j = 0; j < 4; ++j) f[j] = affine_value(cv[j], sa, ws[j], zw[j], ra, za, col[j]);
-            } else {
-#pragma unroll
-              for (int j = 0; j < 4; ++j) f[j] = (float)cv[j] * sa * ws[j];
-            }
-            uint32_t hb[2];
-#pragma unroll
-            for (int j = 0; j < 4; j += 2)
-              hb[j / 2] = __half_as_ushort(__float2half_rn(f[j])) |
-                          ((uint32_t)__half_as_ushort(__float2half_rn(f[j + 1])) << 16);
-            if (full)
-              int8::store8(g.c_fp16 + o, hb[0], hb[1]);
-            else
-              for (int j = 0; j < 4 && ncol + j < g.N; ++j)
-                g.c_fp16[o + j] = __ushort_as_half((unsigned short)(hb[j / 2] >> (16 * (j % 2))));
-          }
+          for (int j = 0; j < 4; j += 2)
+            hb[i][j / 2] = __half_as_ushort(__float2half_rn(f[j])) |
+                           ((uint32_t)__half_as_ushort(__float2half_rn(f[j + 1])) << 16);
         }
+        store_block(g, hb, m0 + row0, ncol, inside);
       }
       __builtin_amdgcn_s_waitcnt(0xc07f);  // reads done before the slot is rewritten
       __builtin_amdgcn_wave_barrier();

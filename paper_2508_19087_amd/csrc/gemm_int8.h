@@ -103,18 +103,73 @@ typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// One 16-byte streaming global store of output bytes (written once, not
-// re-read), at any int32.  As a plain store the compiler shares the first
-// element's store with the element-wise edge path and splits the vector into
-// 12 + 4 bytes.
+// Four int32 outputs of a row in one 16-byte global store, at any int32 (written
+// once, not re-read): streaming where rows start 16-byte aligned.  Elsewhere a
+// row's 32 columns share their two end lines with the tiles beside them, and
+// streamed pieces of a line leave the cache before the others come: int32 2229 x
+// 7605 x 399 W3A4 from fp16 54.3 us streamed, 30.6 us so.  The empty instructions keep
+// the plain store from being merged with the element-wise edge path's first one,
+// which splits the vector into 12 + 4 bytes.
 typedef int any_v4i __attribute__((ext_vector_type(4), aligned(4)));
+template <bool kStream>
 __device__ __forceinline__ void store16(int32_t* p, v4i v) {
-  __builtin_nontemporal_store(v, reinterpret_cast<any_v4i*>(p));
+  if (kStream) {
+    __builtin_nontemporal_store(v, reinterpret_cast<any_v4i*>(p));
+  } else {
+    asm volatile("");
+    *reinterpret_cast<any_v4i*>(p) = v;
+    asm volatile("");
+  }
 }
 // Four halves at any half.
 typedef uint32_t any_v2u __attribute__((ext_vector_type(2), aligned(2)));
 __device__ __forceinline__ void store8(__half* p, uint32_t lo, uint32_t hi) {
   *reinterpret_cast<any_v2u*>(p) = any_v2u{lo, hi};
+}
+
+// A lane's part of a 32 x 32 block of outputs: columns ncol .. ncol + 3 of the rows
+// m, m + 8, m + 16 and m + 24, as int32 and as pairs of halves.  `inside` (uniform):
+// the whole block lies inside the matrix and is stored without a branch per row,
+// which cost 3 to 4% where K is small.
+__device__ __forceinline__ void store_block(const GemmArgs& g, const int32_t (&cv)[4][4], int m, int ncol, bool inside,
+                                            bool stream) {
+  int32_t* const p = g.c_int32 + (int64_t)m * g.N + ncol;
+  const int64_t step = (int64_t)8 * g.N;
+  auto row = [&](int i) { return v4i{cv[i][0], cv[i][1], cv[i][2], cv[i][3]}; };
+  if (inside && stream) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store16<true>(p + i * step, row(i));
+  } else if (inside) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store16<false>(p + i * step, row(i));
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (m + 8 * i < g.M && ncol < g.N) {
+        if (ncol + 3 < g.N)
+          store16<false>(p + i * step, row(i));
+        else
+          for (int j = 0; j < 4 && ncol + j < g.N; ++j) p[i * step + j] = cv[i][j];
+      }
+  }
+}
+__device__ __forceinline__ void store_block(const GemmArgs& g, const uint32_t (&hb)[4][2], int m, int ncol, bool inside) {
+  __half* const p = g.c_fp16 + (int64_t)m * g.N + ncol;
+  const int64_t step = (int64_t)8 * g.N;
+  if (inside) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) store8(p + i * step, hb[i][0], hb[i][1]);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (m + 8 * i < g.M && ncol < g.N) {
+        if (ncol + 3 < g.N)
+          store8(p + i * step, hb[i][0], hb[i][1]);
+        else
+          for (int j = 0; j < 4 && ncol + j < g.N; ++j)
+            p[i * step + j] = __ushort_as_half((unsigned short)(hb[i][j / 2] >> (16 * (j % 2))));
+      }
+  }
 }
 
 // An empty instruction that reads x: code computing x cannot be moved past it.
@@ -145,6 +200,7 @@ struct Int8Params {
   v4i* partial;       // stream-K: two partial tiles per workgroup (workspace)
   uint32_t partial_bytes;
   int* counters;      // stream-K: arrivals per stream-K tile (workspace, zeroed per call)
+  int stream_out;     // int32 rows start 16-byte aligned: their stores stream past the caches
 };
 
 // Bytes of the activation fragment buffer for M rows and K in operand format
@@ -687,7 +743,7 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
       F ? (uint32_t)(NC * kChunk - g.K) * ((1u << P) - 1u) * ((1u << q) - 1u)
         : 4u * (uint32_t)(NC * kChunk - g.K) * (uint32_t)((q == 8 ? -128 : 0) * pad_of(P));
   const uint32_t const_term = ca * cw * (uint32_t)g.K + pad_term;
-  const bool fp16 = g.c_fp16 != nullptr;
+  const bool fp16 = g.c_fp16 != nullptr, stream = prm.stream_out != 0;
 
   // Epilogue terms of tile (m0, n0): one value per thread, fetched a pair of
   // chunks before the tile's flush and written to LDS before that pair's
@@ -798,7 +854,6 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
         __builtin_amdgcn_wave_barrier();
         const int nl = wn * WTN + b * 32 + ec;  // column in the tile
         const int ncol = n0 + nl;
-        const bool full = ncol + 3 < g.N;
         const v4u wt = *reinterpret_cast<const v4u*>(lds_wt + nl);
         const v4f ws = *reinterpret_cast<const v4f*>(lds_ws + nl);
         // the block's four rows and their row terms are read together, before
@@ -813,50 +868,37 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) keep_here(dv[i], atv[i]);
+        int32_t cv[4][4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int ml = wm * WTM + a * 32 + er + 8 * i;  // row in the tile
-          const int m = m0 + ml;
-          const v4i d = dv[i];
-          const uint32_t at = atv[i];
-          int32_t cv[4];
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) cv[j] = (int32_t)(kMul * (uint32_t)d[j] + at + wt[j]);
-          if (m < g.M && ncol < g.N) {
-            const int64_t o = (int64_t)m * g.N + ncol;
-            if (g.c_int32) {
-              if (full)
-                store16(g.c_int32 + o, v4i{cv[0], cv[1], cv[2], cv[3]});
-              else
-                for (int j = 0; j < 4 && ncol + j < g.N; ++j) g.c_int32[o + j] = cv[j];
+          for (int j = 0; j < 4; ++j) cv[i][j] = (int32_t)(kMul * (uint32_t)dv[i][j] + atv[i] + wt[j]);
+        const int row0 = wm * WTM + a * 32 + er;  // row in the tile of cv[0]; cv[i]'s is 8 i further
+        const bool inside = m0 + wm * WTM + a * 32 + 32 <= g.M && n0 + wn * WTN + b * 32 + 32 <= g.N;
+        if (g.c_int32 != nullptr) store_block(g, cv, m0 + row0, ncol, inside, stream);
+        if (fp16) {
+          uint32_t hb[4][2];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int ml = row0 + 8 * i;
+            const float sa = lds_as[ml];
+            float f[4];
+            if (affine) {
+              const v4f zw = *reinterpret_cast<const v4f*>(lds_zt + nl);
+              const v4f col = *reinterpret_cast<const v4f*>(lds_zc + nl);
+              const float ra = lds_zt[BN + ml], za = lds_zc[BN + ml];
+#pragma unroll
+              for (int j = 0; j < 4; ++j) f[j] = affine_value(cv[i][j], sa, ws[j], zw[j], ra, za, col[j]);
+            } else {
+#pragma unroll
+              for (int j = 0; j < 4; ++j) f[j] = (float)cv[i][j] * sa * ws[j];
             }
-            if (fp16) {
-              const float sa = lds_as[ml];
-              float f[4];
-              if (affine) {
-                const v4f zw = *reinterpret_cast<const v4f*>(lds_zt + nl);
-                const v4f col = *reinterpret_cast<const v4f*>(lds_zc + nl);
-                const float ra = lds_zt[BN + ml], za = lds_zc[BN + ml];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) f[j] = affine_value(cv[j], sa, ws[j], zw[j], ra, za, col[j]);
-              } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) f[j] = (float)cv[j] * sa * ws[j];
-              }
-              uint32_t hb[2];
-#pragma unroll
-              for (int j = 0; j < 4; j += 2) {
-                const uint32_t h0 = __half_as_ushort(__float2half_rn(f[j]));
-                const uint32_t h1 = __half_as_ushort(__float2half_rn(f[j + 1]));
-                hb[j / 2] = h0 | (h1 << 16);
-              }
-              if (full)
-                store8(g.c_fp16 + o, hb[0], hb[1]);
-              else
-                for (int j = 0; j < 4 && ncol + j < g.N; ++j)
-                  g.c_fp16[o + j] = __ushort_as_half((unsigned short)(hb[j / 2] >> (16 * (j % 2))));
-            }
+            for (int j = 0; j < 4; j += 2)
+              hb[i][j / 2] = __half_as_ushort(__float2half_rn(f[j])) |
+                             ((uint32_t)__half_as_ushort(__float2half_rn(f[j + 1])) << 16);
           }
+          store_block(g, hb, m0 + row0, ncol, inside);
         }
         __builtin_amdgcn_s_waitcnt(0xc07f);  // reads done before the slot is rewritten
         __builtin_amdgcn_wave_barrier();

@@ -222,6 +222,7 @@ hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* wo
     p.sk_pairs = pl[i].sk_pairs;
     p.sk_grid = pl[i].sk_grid;
     p.partial_bytes = (uint32_t)pl[i].partial_bytes;
+    p.stream_out = g.N % 4 == 0 && (reinterpret_cast<uintptr_t>(g.c_int32) & 15) == 0;
   }
   // Counters of all launches first (one clearing pass), then partial tiles.
   counters = reinterpret_cast<int*>(base);
