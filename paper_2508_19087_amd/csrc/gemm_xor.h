@@ -105,8 +105,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t xor_rsrc(const void* base, uin
 // exactly; a zero weight word meets a zero activation word in the chunks
 // between K and the end of the last round, which adds nothing to any
 // popcount.
+// Waves per SIMD that an instance's registers have to leave room for, with rows
+// from fp16 at up to 2 bits: three at 8 rows (168 registers), and at one row four
+// where the plain form fits (128).  A few registers more are a wave less: W1A1 2 x
+// 18304 x 512 7.6 us with two waves, 6.0 with three; W4A1 8 x 10624 x 256 12.2 us
+// with three, 10.6 with four.  The other instances take what they need.
+constexpr int min_waves(int p, int q, int mt, bool deep, int src) {
+  if (src != kSrcHalf || q > 2) return 1;
+  if (mt == 8) return 3;
+  return !deep && (p == 2 || p == 4 || (p == 8 && q == 1)) ? 4 : 1;
+}
+
 template <int P, int Q, int MT, bool DEEP, bool kALds, int SRC = kSrcPacked>
-__global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams prm) {
+__global__ __launch_bounds__(kWave* kMaxWaves, min_waves(P, Q, MT, DEEP, SRC)) void gemm_xor_kernel(XorParams prm) {
   static_assert(SRC == kSrcPacked || kALds, "the fused source builds the LDS copy");
   extern __shared__ uint4 a_lds[];
   const GemmArgs& g = prm.g;
@@ -293,11 +304,7 @@ __global__ __launch_bounds__(kWave* kMaxWaves) void gemm_xor_kernel(XorParams pr
     for (int m = 0; m < kSrcRows; ++m) {
       if (m >= mrows) break;  // uniform
       rowcode::Quantizer qz{};
-      if (SRC == kSrcHalf) {
-        qz = s_qz[m];
-        qz.b = Q;
-        qz.quick = __builtin_amdgcn_readfirstlane(qz.quick);
-      }
+      if (SRC == kSrcHalf) qz = s_qz[m].uniform(Q);
 #pragma unroll
       for (int r = 0; r < kHeld; ++r)
         if (r < src_rounds) convert(m, r, sd[m][r], qz);

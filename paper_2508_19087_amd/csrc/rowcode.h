@@ -98,6 +98,8 @@ struct Quantizer {
   float rh, s2, base;
   uint32_t least;  // -s in both halves of a dword
 
+  __device__ static __forceinline__ float base_of(int b) { return (float)((b == 8 ? 256 : 128) + (1 << (b - 1))); }
+
   __device__ __forceinline__ void set(uint32_t absmax_bits, int bits) {
     b = bits;
     const float absmax = __half2float(__ushort_as_half((unsigned short)absmax_bits));
@@ -107,16 +109,31 @@ struct Quantizer {
     rh = s > 0.0f ? __fdiv_rn(1.0f, s) * 0.5f : 0.0f;
     s2 = s * 2.0f;
     quick = scale - 0x0400u < 0x7800u;  // normal and finite (uniform where the row is)
-    base = (float)((b == 8 ? 256 : 128) + (1 << (b - 1)));
+    base = base_of(b);
     least = (0x8000u | scale) * 0x00010001u;
   }
 
+  // The same quantizer, read back from LDS for a row that the whole wave shares:
+  // its fields in scalar registers.
+  __device__ __forceinline__ Quantizer uniform(int bits) const {
+    auto first = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); };
+    Quantizer r;
+    r.scale = (uint16_t)first(scale);
+    r.b = bits;
+    r.quick = first(quick) != 0u;
+    r.rh = __builtin_bit_cast(float, first(__builtin_bit_cast(uint32_t, rh)));
+    r.s2 = __builtin_bit_cast(float, first(__builtin_bit_cast(uint32_t, s2)));
+    r.base = base_of(bits);
+    r.least = first(least);
+    return r;
+  }
+
   // Short form: f[j], whose bits 16..23 are the word of value j.
-  template <bool kEight>  // b == 8
-  __device__ __forceinline__ void quick_bits(const uint32_t d[8], uint32_t f[16]) const {
+  template <bool kEight, int kDwords = 8>  // b == 8
+  __device__ __forceinline__ void quick_bits(const uint32_t* d, uint32_t* f) const {
     typedef short short2_t __attribute__((ext_vector_type(2)));
 #pragma unroll
-    for (int t = 0; t < 8; ++t) {
+    for (int t = 0; t < kDwords; ++t) {
       const half2_t x0 = __builtin_bit_cast(half2_t, d[t]) + half2_t{(_Float16)0.0f, (_Float16)0.0f};
       const half2_t x = __builtin_bit_cast(
           half2_t, __builtin_elementwise_max(__builtin_bit_cast(short2_t, x0), __builtin_bit_cast(short2_t, least)));
@@ -132,11 +149,13 @@ struct Quantizer {
   // The 16 words of a lane, element 4 t + i in byte i of u[t].
   __device__ __forceinline__ void words(const uint32_t d[8], uint32_t u[4]) const {
     if (quick) {
-      uint32_t f[16];
-      if (b == 8) quick_bits<true>(d, f);
-      else quick_bits<false>(d, f);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) u[t] = gather(f + 4 * t);
+      for (int t = 0; t < 4; ++t) {
+        uint32_t f[4];
+        if (b == 8) quick_bits<true, 2>(d + 2 * t, f);
+        else quick_bits<false, 2>(d + 2 * t, f);
+        u[t] = gather(f);
+      }
     } else {
       exact_words(d, u);
     }
