@@ -245,6 +245,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
     constexpr int kHalfStride = 64 * 2 + 16;
 #pragma unroll
     for (int a = 0; a < kMF; ++a) {
+      if (m0 + a * 32 >= g.M || n0 + wave * 64 >= g.N) continue;  // uniform: no output here
       const int ml = a * 32 + r;
       const uint32_t at = s_term[kBN + ml];
       const float sa = s_scale[kBN + ml];
@@ -297,6 +298,7 @@ __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Param
   for (int a = 0; a < kMF; ++a) {
 #pragma unroll
     for (int b = 0; b < kNF; ++b) {
+      if (m0 + a * 32 >= g.M || n0 + wave * 64 + b * 32 >= g.N) continue;  // uniform: no output here
       const v16i d = __builtin_convertvector(acc[b][a] * 64.0f, v16i);  // sum of u_a u_w
 #pragma unroll
       for (int gi = 0; gi < 4; ++gi)

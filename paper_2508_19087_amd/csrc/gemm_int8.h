@@ -130,7 +130,8 @@ __device__ __forceinline__ void store8(__half* p, uint32_t lo, uint32_t hi) {
 // A lane's part of a 32 x 32 block of outputs: columns ncol .. ncol + 3 of the rows
 // m, m + 8, m + 16 and m + 24, as int32 and as pairs of halves.  `inside` (uniform):
 // the whole block lies inside the matrix and is stored without a branch per row,
-// which cost 3 to 4% where K is small.
+// which cost 3 to 4% where K is small.  (Blocks wholly outside do not come here: the
+// caller skips them, of 12 rows three in four.)
 __device__ __forceinline__ void store_block(const GemmArgs& g, const int32_t (&cv)[4][4], int m, int ncol, bool inside,
                                             bool stream) {
   int32_t* const p = g.c_int32 + (int64_t)m * g.N + ncol;
@@ -829,6 +830,7 @@ __device__ __forceinline__ void gemm_int8_body(const Int8Params& prm, uint8_t* l
     for (int a = 0; a < FM; ++a) {
 #pragma unroll
       for (int b = 0; b < FN; ++b) {
+        if (m0 + wm * WTM + a * 32 >= g.M || n0 + wn * WTN + b * 32 >= g.N) continue;  // uniform: no output here
         for (int v = pv_first; v <= pv_last; ++v) {
           if (v == st.w) continue;
           const uint32_t so = (uint32_t)(v == pv_first ? 2 * v + 1 : 2 * v) * kSlotBytes;
