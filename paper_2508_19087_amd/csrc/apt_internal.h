@@ -135,7 +135,7 @@ hipError_t launch_gemm_thin(const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_thin_act(const GemmArgs& g, const void* a_src, bool fp16_src, uint16_t* a_scale_out,
                                 hipStream_t s);
 bool thin_preferred(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool unpacked);
-// Modelled microseconds of the XOR + popcount kernel (select.hip).
+// Modelled microseconds of the XOR + popcount kernel.
 double model_xor_us(int M, int N, int K, int p, int q);
 // Compute units of the current device (select.hip).
 int compute_units();

@@ -81,10 +81,13 @@ hipError_t launch(const GemmArgs& g, const void* a_src, int src, uint16_t* a_sca
 
 // Modelled microseconds on packed activations, infinity where the kernel does
 // not take the problem: the launch, the operands' build (per 16-token tile and
-// K group), the items' work (instructions of a word's rebuild, MFMAs per token
-// tile) and the weight stream (re-reads by further rows of workgroups are
-// served by the caches).  Least-squares fits to cold timings on MI355X over
-// M = 2..512, N and K = 512..11008 and p, q = 1..8 (median error 4%; bytes 9%).
+// K group), the items' work (a word's rebuild, which grows with the weight bits,
+// and the MFMAs of each token tile) and the weight stream (re-reads by further
+// rows of workgroups are served by the caches).  Least squares on the relative
+// error over cold timings on MI355X: six-bit operands M = 2..512, N and K =
+// 512..11008 (median error 6%); bytes 651 problems with M = 2..512, N = 128..22016, K =
+// 128..8192, weights of 1 to 8 bits (median error 5%, up to 32 rows of workgroups
+// among them: W4A8 400 x 1024 x 8192 18.1 us modelled, 16.4 measured).
 double thin_us(int M, int N, int K, int p, int q, bool unpacked) {
   ThinLaunch L;
   if (!plan(M, N, K, p, q, unpacked ? thin::kSrcHalf : thin::kSrcPacked, &L)) return HUGE_VAL;
@@ -92,7 +95,7 @@ double thin_us(int M, int N, int K, int p, int q, bool unpacked) {
   constexpr double kRebuild[5] = {0, 7, 10, 18, 22};
   return L.cls == thin::kLow
              ? 2.61 + 0.886 * ops + items * (0.0115 * kRebuild[p] + 0.233 * L.mt) + 0.178 * mb
-             : 1.58 + 2.5 * ops + 1.39 * items + 0.10 * mb + 0.019 * mb * (L.blocks - 1);
+             : 2.96 + 1.35 * ops + items * (0.119 * p + 0.284 * L.mt) + 0.071 * mb;
 }
 
 hipError_t launch_gemm_thin(const GemmArgs& g, hipStream_t s) {

@@ -109,6 +109,24 @@ bool xor_act_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg
   return L.lds && L.grid.x <= 0x7fffffffu && L.grid.y <= 65535u;
 }
 
+// Modelled microseconds of XOR + popcount on packed activations.  Up to 8
+// tokens: a fixed part, the weight stream and the popcounts (least squares on the
+// relative error over cold timings of M = 2..8, N, K = 512..11008, p*q = 1..16:
+// median error 6%).  Above, per launch shape: a fixed part, what one wave takes for
+// its rounds and popcounts, and what the waves cost together (1024 at a time), so
+// that neither a few long waves nor many short ones come out too low (cold timings
+// of M = 9..512, N = 128..12288, K = 128..11008, p*q = 1..64, 2 to 60 us: median error
+// 10% with one row per wave, 7% with eight; 200 us still within 20%).
+double model_xor_us(int M, int N, int K, int p, int q) {
+  if (M <= 8) return 2.55 + (double)N * K * (0.0256e-6 * p + (double)M * q * (1.42 * p + 4.23) * 1e-9);
+  const int groups = padded_rows(N) / kRowGroup;
+  const int rounds = xorpop::staged_chunks(num_chunks(K)) / xorpop::kChunkLanes;
+  const int mt = auto_mt(M, groups, rounds, xorpop::kSrcPacked);
+  const double waves = (double)groups * ((M + mt - 1) / mt) / 1024.0, pops = (double)rounds * p * q;
+  return mt == 1 ? 2.11 + 0.306 * rounds + 0.0163 * pops + waves * (0.384 + 0.0208 * pops)
+                 : 2.72 + 0.286 * rounds + 0.0353 * pops + waves * (0.473 + 0.165 * pops);
+}
+
 // The few-token GEMM on the matrix cores takes the call when the config leaves
 // the launch shape open and it is the faster one (cold weights on MI355X).  One
 // token stays on XOR + popcount, which has every weight load in flight at once
@@ -118,16 +136,31 @@ bool xor_act_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg
 // 34.7 against 11.4 for eight; W2A2 1024 x 1024 the other way round, 2.7 against
 // 3.9 us for eight.  Up to 8 tokens the two models are compared (the XOR one is
 // 10% high where they meet), except where one token per wave makes many waves
-// (W1A1 4096 x 1024, 8 tokens: 4.6 against 3.9); above, XOR keeps the small
-// problems (32 tokens at 1024 x 1024, W2A2: 3.8 against 4.9; 64 tokens at
-// 4096 x 1024: 15.6 against 7.4).
+// (W1A1 4096 x 1024, 8 tokens: 4.6 against 3.9).  Above, the models again, at a
+// margin of 5% for XOR's wider spread: W2A2 55 x 721 x 256 4.7 us on XOR against 6.6,
+// W4A4 64 x 4096 x 1024 15.6 against 7.4 (2000 problems of 9 to 512 tokens: 0.5% above
+// the faster of the two on average; 1.6% with a line on M N and M N K p q alone,
+// which lost up to 40% on small problems).
 bool thin_preferred(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool unpacked) {
   if (M < 2 || cfg.mt != 0 || cfg.waves_m != 0 || cfg.waves_n != 0) return false;
   const double us = thin_us(M, N, K, p, q, unpacked);
   if (us == HUGE_VAL) return false;
-  if (M > 8) return (int64_t)M * N > 32768 || (double)M * N * K * p * q > 6e8;
+  if (M > 8) return 0.95 * us < model_xor_us(M, N, K, p, q);
   return (N < 8192 && M * N >= 32768) || us < 0.9 * model_xor_us(M, N, K, p, q);
 }
+
+}  // namespace apt
+
+// For the tests, not part of the C ABI: whether the XOR route with its launch shape
+// open runs the few-token GEMM (1) or XOR + popcount (0).  Host-only.
+extern "C" int apt_test_few_token(int M, int N, int K, int p, int q, int unpacked) {
+  apt_config_t c{};
+  c.route = APT_ROUTE_XOR;
+  return apt::thin_preferred(M, N, K, p, q, c, unpacked != 0) ? 1 : 0;
+}
+
+namespace apt {
+
 
 namespace {
 

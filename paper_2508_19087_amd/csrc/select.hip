@@ -151,16 +151,18 @@ double model_loop_us(const Int8Shape& s, int f, int M, int N, int K, int grid, i
 }
 
 // Modelled microseconds of gemm_direct.h's kernel (six-bit codes, 128 x 256
-// tiles, two workgroups per compute unit): microseconds per chunk pair with the
-// compute unit full and with a workgroup alone on it (M = 2048, N = 8192 and
-// 4096, the slope between K = 2048 and 6144: W2A2 1.32 and 1.05, W4A4 1.92 and
-// 1.38), and a fixed part that grows with the output written at the end.
+// tiles, two workgroups per compute unit), the launch that writes its fragments
+// included: a fixed part, and microseconds per chunk pair with the compute unit
+// full and with a workgroup alone on it.  Least squares on the relative error over
+// 1800 problems on packed rows with cold weights (M = 9..4096, N, K = 128..12288, p,
+// q = 1..4; median error 8%), less the part that grows with the output, which the
+// other shapes' figures leave out as well.  The fixed part keeps small problems
+// off the kernel: 128 x 256 x 256 takes 11 us on it and 3 to 5 on the XOR route.
 double model_six_us(int M, int N, int K, int p, int cus) {
   const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 255) / 256), pairs = (num_chunks(K) + 1) / 2;
-  const double pair = p <= 2 ? 1.32 : 1.92, alone = p <= 2 ? 1.05 : 1.38;
+  const double pair = p <= 2 ? 1.35 : 1.66, alone = p <= 2 ? 0.91 : 1.20;
   const int64_t full = tiles / (2 * cus), rem = tiles % (2 * cus);
-  return (double)pairs * (full * pair + (rem == 0 ? 0.0 : rem <= cus ? alone : pair)) +
-         2.5 + 0.025 * (double)std::min<int64_t>(tiles, 700);
+  return 9.0 + (double)pairs * (full * pair + (rem == 0 ? 0.0 : rem <= cus ? alone : pair));
 }
 
 // Weights of 7 and 8 bits on the 512 x 128 shape in one round that leaves
@@ -179,23 +181,6 @@ double model_tall_us(int K) { return 1.10 * (((num_chunks(K) + 1) / 2) * 3.3 + 1
 double model_us(const Int8Shape& s, int f, int M, int N, int K, int grid, int cus) {
   return model_loop_us(s, f, M, N, K, grid, cus) + s.t[f].fixed_us;
 }
-
-}  // namespace
-
-// Modelled microseconds of the XOR route: a fixed part, and for up to 8 tokens
-// the weight stream and the popcounts (least squares on the relative error over
-// cold timings of M = 2..8, N, K = 512..11008, p*q = 1..16: median error 6%);
-// above that a cost per 32-bit word pair of an 8-row activation block and one
-// weight row, rising with the activation planes read from LDS (q) and with the
-// p*q plane products (M = 16 to 256, N and K from 1024 to 14336, p*q from 2 to
-// 16: median error 8%).
-double model_xor_us(int M, int N, int K, int p, int q) {
-  if (M <= 8) return 2.55 + (double)N * K * (0.0256e-6 * p + (double)M * q * (1.42 * p + 4.23) * 1e-9);
-  const double words = 8.0 * ((M + 7) / 8) * (double)N * K / 32.0;
-  return 3.564 + words * (-0.2140 + 0.1792 * q + 0.0439 * p * q) * 1e-6;
-}
-
-namespace {
 
 // The tail shape a split config with main shape i and tail size of shape t
 // runs: of the shapes of that size, the one with the main shape's wave count
@@ -454,12 +439,9 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
   // costs.  The MFMA figures were measured with every compute unit
   // busy and overstate grids of a few tiles by 10-40%, so they count at 90%
   // here (measured over M = 16..256, N, K = 1024..14336, p*q = 2..16).
-  // XOR + popcount itself only inside the range its model was fitted over
-  // (W1A1 1024 x 4096 x 4096, far outside, takes 266 us where 8 were modelled).
   const apt_config_t open = base_config(APT_ROUTE_XOR);
   const double few = thin_preferred(M, N, K, p, q, open, false) ? thin_us(M, N, K, p, q, false)
-                     : M <= 256 && (p * q >= 2 || (int64_t)M * N <= 32768) ? model_xor_us(M, N, K, p, q)
-                                                                           : HUGE_VAL;
+                                                                : model_xor_us(M, N, K, p, q);
   if (few < 0.9 * best) return open;
   const Int8Shape& s = kInt8Shapes[best_i];
   apt_config_t c = base_config(best_fp4 ? APT_ROUTE_FP4_MFMA : APT_ROUTE_INT8_MFMA);
