@@ -206,7 +206,8 @@ apt_status_t apt_select_config(int M, int N, int K, int p, int q, apt_config_t* 
  * 256; the FP4 MFMA route with q <= 2 stores half of that: two values per
  * byte) and,
  * for each launch with a stream-K decomposition (grid > 0 and T not a
- * multiple of grid), two int32 BM x BN partial tiles per workgroup and one
+ * multiple of grid; none where 256x128 with 4x1 waves runs six-bit operands),
+ * two int32 BM x BN partial tiles per workgroup and one
  * counter per shared tile, each region rounded up to 256 bytes; the other
  * routes need 0.  Returns 0 for invalid sizes or configs. */
 size_t apt_gemm_workspace_bytes(int M, int N, int K, int p, int q, const apt_config_t* cfg);

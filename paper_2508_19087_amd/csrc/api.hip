@@ -125,7 +125,7 @@ size_t apt_gemm_workspace_bytes(int M, int N, int K, int p, int q, const apt_con
                              : *cfg;
   if (!apt::mfma_route(c.route)) return 0;
   if (check_config(c, M, N, K, p, q, true) != APT_OK) return 0;
-  return apt::int8_workspace_bytes(M, N, K, q, c);
+  return apt::int8_workspace_bytes(M, N, K, p, q, c);
 }
 
 }  // extern "C"
@@ -154,9 +154,9 @@ apt_status_t gemm_check(int M, int N, int K, int p, int q, const void* a_packed,
   return APT_OK;
 }
 
-size_t gemm_workspace_need(int M, int N, int K, int q, const apt_config_t& c) {
+size_t gemm_workspace_need(int M, int N, int K, int p, int q, const apt_config_t& c) {
   if (!mfma_route(c.route)) return 0;
-  return int8_workspace_bytes(M, N, K, q, c);
+  return int8_workspace_bytes(M, N, K, p, q, c);
 }
 
 apt_status_t gemm_launch(int M, int N, int K, int p, int q, const void* a_packed,
@@ -165,7 +165,7 @@ apt_status_t gemm_launch(int M, int N, int K, int p, int q, const void* a_packed
                          uint16_t* c_fp16, const uint16_t* a_zero, const uint16_t* w_zero,
                          const apt_config_t& c, void* workspace, size_t workspace_bytes,
                          void* stream) {
-  const size_t need = gemm_workspace_need(M, N, K, q, c);
+  const size_t need = gemm_workspace_need(M, N, K, p, q, c);
   if (need > 0) {
     if (workspace == nullptr || workspace_bytes < need) return APT_ERR_WORKSPACE;
     if (!aligned16(workspace)) return APT_ERR_INVALID_ARG;
@@ -238,7 +238,7 @@ ActLayout act_layout(int M, int N, int K, int p, int q, bool fp16, const apt_con
   const bool frags = c.route == APT_ROUTE_INT8_MFMA && int8_operand_format(c, q) == 0 &&
                      (int64_t)M * K * (fp16 ? 2 : 1) < ((int64_t)1 << 31);
   L.plan = frags ? ActPlan::kFragments : ActPlan::kPack;
-  L.route_bytes = align256(gemm_workspace_need(M, N, K, q, c));
+  L.route_bytes = align256(gemm_workspace_need(M, N, K, p, q, c));
   size_t off = L.route_bytes;
   L.planes_off = off;
   if (!frags) off += align256(apt_packed_bytes(M, K, q));
@@ -417,7 +417,7 @@ size_t apt_search_workspace_bytes(int M, int N, int K, int p, int q) {
   for (int i = 0; i < n; ++i)
     if (apt::mfma_route(cand[i].route) &&
         apt::int8_config_ok(cand[i], N))
-      most = std::max(most, apt::int8_workspace_bytes(M, N, K, q, cand[i]));
+      most = std::max(most, apt::int8_workspace_bytes(M, N, K, p, q, cand[i]));
   return most;
 }
 

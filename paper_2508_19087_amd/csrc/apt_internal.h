@@ -167,7 +167,7 @@ bool int8_runs_direct(const apt_config_t& cfg, int K, int p, int q);
 constexpr int kMaxGrid = 4096;  // persistent workgroups of the int8 route, at most
 bool int8_config_ok(const apt_config_t& cfg, int N);
 bool int8_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg);
-size_t int8_workspace_bytes(int M, int N, int K, int q, const apt_config_t& cfg);
+size_t int8_workspace_bytes(int M, int N, int K, int p, int q, const apt_config_t& cfg);
 
 // Plane-pair +-1 MFMA route (gemm_pm1.hip).
 hipError_t launch_gemm_pm1(const GemmArgs& g, const apt_config_t& cfg, hipStream_t stream);
@@ -189,7 +189,7 @@ apt_status_t gemm_check(int M, int N, int K, int p, int q, const void* a_packed,
                         const void* w_packed, const int32_t* a_rowsum, const int32_t* w_rowsum,
                         const int32_t* c_int32, const uint16_t* a_scale, const uint16_t* w_scale,
                         const uint16_t* c_fp16, const apt_config_t* cfg, apt_config_t* resolved);
-size_t gemm_workspace_need(int M, int N, int K, int q, const apt_config_t& c);
+size_t gemm_workspace_need(int M, int N, int K, int p, int q, const apt_config_t& c);
 apt_status_t gemm_launch(int M, int N, int K, int p, int q, const void* a_packed,
                          const void* w_packed, const int32_t* a_rowsum, const int32_t* w_rowsum,
                          int32_t* c_int32, const uint16_t* a_scale, const uint16_t* w_scale,

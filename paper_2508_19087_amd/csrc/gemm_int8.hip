@@ -173,10 +173,20 @@ bool int8_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg) {
          int8::a_frag_bytes(M, K, int8::operand_format(cfg, q)) < limit;
 }
 
+// The 256 x 128 (4 x 1) shape of the int8 route, in one launch, where the
+// operands fit six-bit codes and the fp32 sums stay exact: gemm_direct.h, with one
+// workgroup per tile whatever the config's grid.
+bool int8_runs_direct(const apt_config_t& cfg, int K, int p, int q) {
+  return cfg.route == APT_ROUTE_INT8_MFMA && cfg.split_n == 0 && int8::shape_index(cfg) == int8::kDirectShape &&
+         six_bit_ok(K, p, q);
+}
+
 // Workspace: activation fragments, then per launch (stream-K) one arrival
 // counter per stream-K tile, then per launch two int32 partial tiles per
-// workgroup.
-size_t int8_workspace_bytes(int M, int N, int K, int q, const apt_config_t& cfg) {
+// workgroup.  gemm_direct.h's kernel shares no tile: fragments alone, at the
+// documented size of the route's (its own take three quarters of that).
+size_t int8_workspace_bytes(int M, int N, int K, int p, int q, const apt_config_t& cfg) {
+  if (int8_runs_direct(cfg, K, p, q)) return int8::align256(int8::a_frag_bytes(M, K));
   int8::Plan pl[2];
   const int n = int8::make_plans(M, N, K, cfg, pl);
   size_t bytes = int8::align256(int8::a_frag_bytes(M, K, int8::operand_format(cfg, q)));
@@ -187,21 +197,15 @@ size_t int8_workspace_bytes(int M, int N, int K, int q, const apt_config_t& cfg)
 
 int int8_operand_format(const apt_config_t& cfg, int q) { return int8::operand_format(cfg, q); }
 
-// The 256 x 128 (4 x 1) shape of the int8 route, in one launch, where the
-// operands fit six-bit codes and the fp32 sums stay exact: gemm_direct.h.  Its
-// fragments take three quarters of the workspace that the int8 ones do.
-bool int8_runs_direct(const apt_config_t& cfg, int K, int p, int q) {
-  return cfg.route == APT_ROUTE_INT8_MFMA && cfg.split_n == 0 && int8::shape_index(cfg) == int8::kDirectShape &&
-         six_bit_ok(K, p, q);
-}
-
 hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* workspace,
                             hipStream_t stream, const ActSource* src) {
   using namespace int8;
-  Plan pl[2];
-  const int nl = make_plans(g.M, g.N, g.K, cfg, pl);
-  Int8Params prm[2];
   const bool six = int8_runs_direct(cfg, g.K, g.p, g.q);
+  apt_config_t run = cfg;
+  if (six) run.grid = 0;  // nothing shared: no counters, no partial tiles
+  Plan pl[2];
+  const int nl = make_plans(g.M, g.N, g.K, run, pl);
+  Int8Params prm[2];
   const int fmt = six ? kSixFormat : operand_format(cfg, g.q);
   uint8_t* base = static_cast<uint8_t*>(workspace) + align256(a_frag_bytes(g.M, g.K, fmt));
   int* counters = nullptr;

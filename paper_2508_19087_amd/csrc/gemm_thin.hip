@@ -87,7 +87,7 @@ hipError_t launch(const GemmArgs& g, const void* a_src, int src, uint16_t* a_sca
 // error over cold timings on MI355X: six-bit operands M = 2..512, N and K =
 // 512..11008 (median error 6%); bytes 651 problems with M = 2..512, N = 128..22016, K =
 // 128..8192, weights of 1 to 8 bits (median error 5%, up to 32 rows of workgroups
-// among them: W4A8 400 x 1024 x 8192 18.1 us modelled, 16.4 measured).
+// among them: W4A8 400 x 1024 x 8192 18 us modelled, 16.4 measured).
 double thin_us(int M, int N, int K, int p, int q, bool unpacked) {
   ThinLaunch L;
   if (!plan(M, N, K, p, q, unpacked ? thin::kSrcHalf : thin::kSrcPacked, &L)) return HUGE_VAL;

@@ -62,14 +62,14 @@ extern "C" apt_status_t apt_gemm_noalloc(int M, int N, int K, int p, int q, cons
   apt_status_t st = apt::gemm_check(M, N, K, p, q, a_packed, w_packed, a_rowsum, w_rowsum, c_int32,
                                     a_scale, w_scale, c_fp16, cfg, &c);
   if (st != APT_OK) return st;
-  size_t need = apt::gemm_workspace_need(M, N, K, q, c);
+  size_t need = apt::gemm_workspace_need(M, N, K, p, q, c);
   const bool selected = cfg == nullptr || cfg->route == APT_ROUTE_AUTO;
   if (need > APT_NOALLOC_SCRATCH_BYTES && selected && (c.grid != 0 || c.tail_grid != 0)) {
     // The selected decomposition's stream-K partial tiles do not fit: the same
     // tiles with one workgroup per tile need only the activation fragments.
     c.grid = 0;
     c.tail_grid = 0;
-    need = apt::gemm_workspace_need(M, N, K, q, c);
+    need = apt::gemm_workspace_need(M, N, K, p, q, c);
   }
   if (need > APT_NOALLOC_SCRATCH_BYTES) return APT_ERR_WORKSPACE;
   void* ws = nullptr;

@@ -208,10 +208,9 @@ int split_columns(const Int8Shape& s, int M, int N, int cus) {
 // The shipped lookup table (Sec. V-B keeps the search results for common LLM
 // shapes): the configs the best-kernel search module picked on MI355X for the
 // workload shapes with M > 8 (bench.py --search), keyed by the M bucket
-// ceil(log2 M), N, K, p and q.  Smaller M always takes the XOR route.  The
-// two 11008 x 4096 entries run one persistent round with the leftover tiles
-// chained whole onto its workgroups (measured 3-5% faster than one workgroup
-// per tile; see sk_parts in gemm_int8.hip).
+// ceil(log2 M), N, K, p and q.  Smaller M always takes the XOR route.  (The 256 x
+// 128 entries at up to 4 bits run gemm_direct.h's kernel, which has no grid: the
+// 512 workgroups that the first of them names are not used.)
 struct ShippedEntry {
   int mlog, N, K, p, q;
   apt_config_t cfg;
@@ -303,10 +302,11 @@ int table_size() {
 
 // Every config the search module times for (M, N, K, p, q): the XOR route,
 // the +-1 plane route where its operands fit (p, q <= 7), each int8 tile shape
-// with one workgroup per tile and with a persistent grid of one round of
-// workgroups, and the split launches the model considers (a main shape over
-// whole rounds of columns, a smaller shape on the rest); each of these again
-// on the FP4 route where it applies (FP4 or FP8 activations).
+// with one workgroup per tile and (but for the shape that runs six-bit codes,
+// which has no grid) with a persistent grid of one round of workgroups, and the
+// split launches the model considers (a main shape over whole rounds of columns,
+// a smaller shape on the rest); each of these again on the FP4, FP6 or FP8 route
+// where one applies.
 // The most configs candidate_configs can list: XOR (three launch shapes),
 // +-1 planes, then for each
 // operand format every shape twice and every main shape with every tail.
@@ -332,50 +332,45 @@ int candidate_configs(int M, int N, int K, int p, int q, apt_config_t* out, int 
   }
   if (p <= 7 && q <= 7) add(base_config(APT_ROUTE_PM1_MFMA));
   const int cus = compute_units();
-  auto int8_cfg = [&](const Int8Shape& s, int grid) {
-    apt_config_t c = base_config(APT_ROUTE_INT8_MFMA);
-    c.bm = s.bm;
-    c.bn = s.bn;
-    c.bk = kChunk;
-    c.waves_m = s.wm;
-    c.waves_n = s.wn;
-    c.lds_stages = 3;
-    c.grid = grid;
-    return c;
-  };
-  for (int i = 0; i < kNumInt8Shapes; ++i) {
-    const Int8Shape& s = kInt8Shapes[i];
-    add(int8_cfg(s, 0));
-    add(int8_cfg(s, std::min(cus * s.per_cu, kMaxGrid)));
-  }
-  const int n_int8_single = n;
-  for (int i = 0; i < kNumMainShapes; ++i) {
-    const Int8Shape& s = kInt8Shapes[i];
-    const int split = split_columns(s, M, N, cus);
-    if (split == 0) continue;
-    for (int t = kFirstTail; t < kNumInt8Shapes; ++t) {
-      if (!tail_runs_as(i, t)) continue;
-      apt_config_t c = int8_cfg(s, 0);
-      c.split_n = split;
-      c.tail_bm = kInt8Shapes[t].bm;
-      c.tail_bn = kInt8Shapes[t].bn;
-      add(c);
+  auto tile_cfgs = [&](int route) {
+    auto cfg = [&](const Int8Shape& s, int grid) {
+      apt_config_t c = base_config(route);
+      c.bm = s.bm;
+      c.bn = s.bn;
+      c.bk = kChunk;
+      c.waves_m = s.wm;
+      c.waves_n = s.wn;
+      c.lds_stages = 3;
+      c.grid = grid;
+      return c;
+    };
+    for (int i = 0; i < kNumInt8Shapes; ++i) {
+      const Int8Shape& s = kInt8Shapes[i];
+      const apt_config_t one = cfg(s, 0);
+      add(one);
+      if (!int8_runs_direct(one, K, p, q)) add(cfg(s, std::min(cus * s.per_cu, kMaxGrid)));
     }
-  }
+    for (int i = 0; i < kNumMainShapes; ++i) {
+      const Int8Shape& s = kInt8Shapes[i];
+      const int split = split_columns(s, M, N, cus);
+      if (split == 0) continue;
+      for (int t = kFirstTail; t < kNumInt8Shapes; ++t) {
+        if (!tail_runs_as(i, t)) continue;
+        apt_config_t c = cfg(s, 0);
+        c.split_n = split;
+        c.tail_bm = kInt8Shapes[t].bm;
+        c.tail_bn = kInt8Shapes[t].bn;
+        add(c);
+      }
+    }
+  };
+  tile_cfgs(APT_ROUTE_INT8_MFMA);
   // the same tile configs with FP4 operands where they apply, with FP6
   // operands where those apply and FP4 does not (p or q = 3), and with FP8
   // operands where neither applies (p or q = 4)
-  const int end = n;
-  const int route = fp4_route_ok(K, p, q)   ? APT_ROUTE_FP4_MFMA
-                    : fp6_route_ok(K, p, q) ? APT_ROUTE_FP6_MFMA
-                    : fp8_route_ok(K, p, q) ? APT_ROUTE_FP8_MFMA : 0;
-  if (route != 0) {
-    for (int j = n_int8_single - 2 * kNumInt8Shapes; j < end; ++j) {
-      apt_config_t c = out[j];
-      c.route = route;
-      add(c);
-    }
-  }
+  if (fp4_route_ok(K, p, q)) tile_cfgs(APT_ROUTE_FP4_MFMA);
+  else if (fp6_route_ok(K, p, q)) tile_cfgs(APT_ROUTE_FP6_MFMA);
+  else if (fp8_route_ok(K, p, q)) tile_cfgs(APT_ROUTE_FP8_MFMA);
   return n;
 }
 

@@ -538,3 +538,16 @@ def test_fp8_workspace_and_bound():
     k_ok = ((1 << 24) - 1) // 225 // 128 * 128
     assert apt.apt_gemm_workspace_bytes(64, 64, k_ok, 4, 4, f8) > 0
     assert apt.apt_gemm_workspace_bytes(64, 64, k_ok + 128, 4, 4, f8) == 0
+
+
+@pytest.mark.parametrize("N", [9216, 10240])
+def test_workspace_of_six_bit_tiles_holds_no_partials(N):
+    """The 256x128 shape with 4x1 waves shares no tile at up to 4 bits, whatever its
+    grid: the fragments alone (with 2048 rows and K = 4096, 9216 or 10240 columns
+    leave a persistent round of 512 workgroups shared tiles).  Nor does the shipped
+    entry that matches these sizes ask for more.  Wider operands keep the partials."""
+    make = lambda grid: apt.apt_config_t.make(apt.APT_ROUTE_INT8_MFMA, 256, 128, 128, 4, 1, grid, 3)  # noqa: E731
+    for grid in (0, 300, 512, 4096):
+        assert apt.apt_gemm_workspace_bytes(2048, N, 4096, 4, 4, make(grid)) == 2048 * 4096
+        assert apt.apt_gemm_workspace_bytes(2048, N, 4096, 5, 4, make(grid)) == _int8_workspace(2048, N, 4096, make(grid))
+    assert apt.apt_gemm_workspace_bytes(2048, N, 4096, 4, 4, None) == 2048 * 4096

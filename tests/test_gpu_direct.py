@@ -69,3 +69,20 @@ def test_direct_exact_at_its_bound(p, q, K):
     c32, _ = apt.gemm(a, w, cfg=CFG)
     top = K * ((1 << p) - 1) * ((1 << q) - 1)
     assert (c32.cpu().numpy() == np.array([top, -top, top])).all()
+
+
+@pytest.mark.parametrize("grid", [0, 512])
+def test_direct_stays_inside_its_workspace(grid):
+    """The workspace holds the fragments alone, whatever the grid: 2000 x 1300 outputs
+    whose tiles a persistent round would share, with guard bytes behind."""
+    import torch
+    M, N, K, p, q = 2000, 1300, 300, 4, 3
+    g = synth.rng(122, M, N)
+    wc, ac = synth.uniform_codes(g, N, K, p), synth.uniform_codes(g, M, K, q)
+    w, a = apt.pack(dev(wc), p), apt.pack(dev(ac), q, activations=True)
+    cfg = apt.apt_config_t.make(apt.APT_ROUTE_INT8_MFMA, 256, 128, 128, 4, 1, grid, 3)
+    need = apt.apt_gemm_workspace_bytes(M, N, K, p, q, cfg)
+    ws = torch.full((need + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    c32, _ = apt.gemm(a, w, cfg=cfg, workspace=ws[:need])
+    assert_int32_equal(c32.cpu().numpy(), ref.gemm(ac, wc, p, q), "direct")
+    assert (ws[need:].cpu().numpy() == 0x5A).all()
