@@ -65,7 +65,7 @@ constexpr int kNumMainShapes = 3;
 constexpr int kFirstTail = 2;
 // The shape that runs on six-bit codes where they hold the operands (gemm_direct.h).
 constexpr int kSixShape = 2;
-// The shape with figures of its own in a round that is not full (tall_round).
+// The shape with figures of its own in a partly filled round (tall_round).
 constexpr int kTallShape = 1;
 // Device-wide rate at which stream-K partial tiles are written and read back
 // (bytes per microsecond), as the stream-K launches measured on MI355X show.
@@ -165,16 +165,19 @@ double model_six_us(int M, int N, int K, int p, int cus) {
   return 9.0 + (double)pairs * (full * pair + (rem == 0 ? 0.0 : rem <= cus ? alone : pair));
 }
 
-// Weights of 7 and 8 bits on the 512 x 128 shape in one round that leaves
-// compute units over: a chunk pair takes 3.1 to 3.4 us there, against 4.04 with
-// all of them busy (W8A8, 64 to 192 tiles), so the shape's figures, taken over a
-// full round, overstate it (1024 x 12288 x 4096 95 us modelled, 70 measured
-// against 75 on 128 x 128 tiles).  Only where N has no partial tile: with one the
-// shape measured up to 16% slower than the others (997 x 12234 x 1506 58.7
-// against 49.1 us).  The figures are 10% above the measured ones, since nearer than
-// that the other shapes are as good (1778 x 4736 x 1408 36.0 against 34.7).
+// Weights of 7 and 8 bits on the 512 x 128 shape in one round of at most three
+// quarters of the compute units: a chunk pair takes 3.1 to 3.4 us there, against
+// 4.04 with all of them busy (W8A8, 64 to 192 tiles), so the shape's figures, taken
+// over a full round, overstate it (1024 x 12288 x 4096 95 us modelled, 70 measured
+// against 75 on 128 x 128 tiles).  Over W7 and W8 with A2 to A8 the picks that this
+// changes are 1.09 times as fast (0.97 the least); with more tiles they were 5%
+// slower (W7A7 1643 x 7936 x 5504, 248 tiles, 102 against 96 us; W7A8 1608 x 7936 x
+// 9600 175 against 165).  Only where N has no partial tile: with one the shape
+// measured up to 16% slower than the others (997 x 12234 x 1506 58.7 against 49.1
+// us).  The figures are 10% above the measured ones, since nearer than that the
+// other shapes are as good (1778 x 4736 x 1408 36.0 against 34.7).
 bool tall_round(int M, int N, int p, int cus) {
-  return p >= 7 && N % 128 == 0 && (int64_t)((M + 511) / 512) * (N / 128) < cus;
+  return p >= 7 && N % 128 == 0 && (int64_t)((M + 511) / 512) * (N / 128) * 4 <= (int64_t)cus * 3;
 }
 double model_tall_us(int K) { return 1.10 * (((num_chunks(K) + 1) / 2) * 3.3 + 17.5); }
 

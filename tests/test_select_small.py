@@ -1,5 +1,6 @@
 """The selector on problems too small to pay for the prefill kernels' launches and
-pipelines, and the XOR route's choice between its two kernels.  The model runs on
+pipelines, the XOR route's choice between its two kernels, and the range of the
+tall tiles.  The model runs on
 the host; the problems and the kernel each belongs on were measured on MI355X with
 cold weights (the faster kernel by 20% or more)."""
 import ctypes
@@ -53,3 +54,13 @@ def test_few_tokens_take_the_few_token_kernel(M, N, K, p, q):
 def test_prefill_keeps_the_six_bit_kernel(M, N, K, p, q):
     c = apt.select_config(M, N, K, p, q)
     assert (c.route, c.bm, c.bn, c.waves_m, c.waves_n) == (apt.APT_ROUTE_INT8_MFMA, 256, 128, 4, 1)
+
+
+def test_tall_tiles_only_in_a_partly_filled_round():
+    """512 x 128 tiles at 8 bits up to three quarters of the compute units (192 tiles
+    here); at 248 the 256 x 128 tiles are 5% faster."""
+    c = apt.select_config(1024, 12288, 4096, 8, 8)
+    assert (c.bm, c.bn) == (512, 128)
+    for s in ((1643, 7936, 5504, 7, 7), (1608, 7936, 9600, 7, 8)):
+        c = apt.select_config(*s)
+        assert (c.bm, c.bn) == (256, 128)
