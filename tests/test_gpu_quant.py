@@ -7,7 +7,7 @@ import pytest
 
 import paper_2508_19087_amd as apt
 import synth
-from gpu_util import assert_int32_equal
+from gpu_util import assert_int32_equal, dev
 from oracle import oracle as ref
 
 pytestmark = pytest.mark.gpu
@@ -139,3 +139,30 @@ def test_rows_with_a_value_that_is_not_finite_keep_words_in_range(q, bad):
     for m in (0, 2):
         w, wr, ws, codes = expected(x[m:m + 1], q)
         assert rs[m] == wr[0] and sc[m] == ws[0] and np.array_equal(u[m], ref.convert(codes, q)[0])
+
+
+@pytest.mark.parametrize("q", [1, 4, 7, 8])
+@pytest.mark.parametrize("K", [1040, 1041])
+@pytest.mark.parametrize("bad", [np.inf, np.nan])
+def test_rows_that_are_not_finite_in_every_kernel(q, K, bad):
+    """The fused GEMV, the few-token GEMM and the fragment writer (six-bit and byte
+    operands) decide on the quantizer's form by themselves: a row with an infinity or
+    a NaN keeps its words in range (the product is a sum of K odd numbers of at most
+    (2^p - 1)(2^q - 1)), and the rows beside it are as without it."""
+    p = 4
+    six = apt.apt_config_t.make(apt.APT_ROUTE_INT8_MFMA, 256, 128, 128, 4, 1, 0, 3)
+    tiles = apt.apt_config_t.make(apt.APT_ROUTE_INT8_MFMA, 128, 128, 128, 2, 2, 0, 3)
+    for M, N, cfg in ((3, 65, None), (8, 4100, None), (40, 131, six), (40, 131, tiles)):
+        g = synth.rng(74, M, N, K, q)
+        x = synth.fp16_activations(g, M, K)
+        wc = synth.uniform_codes(g, N, K, p)
+        codes, s16 = ref.quantize_fp16(x, q)
+        x[1, 700] = bad
+        c32, _, sc = apt.gemm_act(dev(x), q, apt.pack(dev(wc), p), cfg=cfg)
+        c32, sc = c32.cpu().numpy(), sc.cpu().numpy()
+        others = np.arange(M) != 1
+        assert np.array_equal(c32[others], ref.gemm(codes, wc, p, q)[others]), (M, N)
+        assert np.array_equal(sc[others].view(np.uint16), s16[others].view(np.uint16)), (M, N)
+        assert not np.isfinite(sc[1])
+        row = c32[1].astype(np.int64)
+        assert (np.abs(row) <= K * 15 * ((1 << q) - 1)).all() and ((row - K) % 2 == 0).all(), (M, N)

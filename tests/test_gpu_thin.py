@@ -3,7 +3,9 @@ its launch shape is left open and it is the faster kernel: every operand class
 and shape built, at the edges of its tiles, K groups and token tiles, from
 packed activations, int8 codes and fp16 values.  int32 equals the oracle and
 the forced XOR + popcount kernel bit for bit, fp16 lies within the epilogue's
-tolerance, fp16 row scales are bit-exact."""
+tolerance, fp16 row scales are bit-exact.  Weights of 5 to 8 bits and activations of
+more than 4 end at K = 8192 (12288 at up to 4 weight bits): past it the same calls
+run XOR + popcount."""
 import numpy as np
 import pytest
 
@@ -11,6 +13,7 @@ import paper_2508_19087_amd as apt
 import synth
 from gpu_util import assert_int32_equal, dev
 from oracle import oracle as ref
+from test_select_small import few_token
 
 pytestmark = pytest.mark.gpu
 
@@ -28,7 +31,9 @@ def check_fp16(c16, C, sa, sw, what):
     assert ref.fp16_close(c16.cpu().numpy(), E).all(), what
 
 
-# N M >= 32768 (N < 8192) or M > 8 with N M > 32768 takes the few-token GEMM
+# most of these take the few-token GEMM (some of those with more than 32 tokens, and
+# the byte operands past K = 8192, run XOR + popcount); test_few_tokens_taken has
+# token tiles and rows of workgroups that all do
 @pytest.mark.parametrize("M,N,K", [
     (8, 4096, 128), (7, 4700, 100), (8, 4097, 513), (5, 6600, 4096), (3, 8191 // 2 * 2 + 2731, 4000),
     (8, 4111, 4097), (8, 4100, 8300), (6, 5500, 12289),        # 2, 3 and 4 K groups per wave
@@ -72,6 +77,48 @@ def test_few_tokens_unpacked(M, N, K, p, q):
     assert np.array_equal(sc.cpu().numpy().view(np.uint16), s16.view(np.uint16)), what
     C = ref.gemm(codes, wc, p, q)
     assert_int32_equal(c32.cpu().numpy(), C, what + " fp16")
+    check_fp16(c16, C, s16, sw, what + " fp16")
+
+
+@pytest.mark.parametrize("M,N,K", [(9, 4100, 4100), (32, 4100, 700), (33, 6100, 1000), (70, 3100, 300), (130, 1030, 2000),
+                                   (512, 300, 1100)])
+@pytest.mark.parametrize("p,q", [(2, 4), (4, 4), (5, 7), (8, 8), (4, 8), (8, 3)])
+def test_few_tokens_taken(M, N, K, p, q):
+    assert few_token(M, N, K, p, q)
+    test_few_tokens_packed(M, N, K, p, q)
+
+
+def taken_unpacked(M, N, K, p, q):
+    assert few_token(M, N, K, p, q, unpacked=True)
+    test_few_tokens_unpacked(M, N, K, p, q)
+
+
+@pytest.mark.parametrize("K", [4096, 4000])
+@pytest.mark.parametrize("p,q", [(2, 4), (4, 4), (5, 7), (8, 8), (4, 8), (8, 3)])
+def test_three_tokens_unpacked(K, p, q):
+    """Two waves per row, the last two with none."""
+    taken_unpacked(3, 11008, K, p, q)
+
+
+@pytest.mark.parametrize("N,K,p,q", [(11008, 4096, 2, 4), (11008, 4096, 4, 4), (11008, 4096, 8, 3), (16500, 2999, 4, 4),
+                                     (16500, 2999, 4, 8), (16500, 2999, 8, 8), (22016, 4097, 5, 7)])
+def test_two_tokens_unpacked(N, K, p, q):
+    """Four waves per row."""
+    assert few_token(2, N, K, p, q, unpacked=True)
+    g = synth.rng(113, N, K, p, q)
+    wc, w, sw = weights(g, N, K, p)
+    ac, sa = synth.uniform_codes(g, 2, K, q), synth.scales(g, 2, *synth.A_SCALE_RANGE)
+    x = synth.fp16_activations(g, 2, K)
+    x[1, 3:] = 0.0
+    codes, s16 = ref.quantize_fp16(x, q)
+    for src, c, s, kw in ((ac, ac, sa, {"a_scale": dev(sa)}), (x, codes, s16, {})):
+        what = "2x%dx%d W%dA%d %s" % (N, K, p, q, src.dtype)
+        c32, c16, sc = apt.gemm_decode(dev(src), q, w, w_scale=dev(sw), out_fp16=True, **kw)
+        C = ref.gemm(c, wc, p, q)
+        assert_int32_equal(c32.cpu().numpy(), C, what)
+        check_fp16(c16, C, s, sw, what)
+        if sc is not None:
+            assert np.array_equal(sc.cpu().numpy().view(np.uint16), s16.view(np.uint16)), what
 
 
 @pytest.mark.parametrize("M", [8, 40])

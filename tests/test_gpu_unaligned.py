@@ -8,6 +8,7 @@ import pytest
 
 import paper_2508_19087_amd as apt
 from test_gpu_act import check
+from test_select_small import few_token
 
 pytestmark = pytest.mark.gpu
 
@@ -23,3 +24,13 @@ def test_rows_at_any_byte(K, fp16_src):
             for offset in (0, 1, 5):
                 check(M, N, K, p, q, cfg=cfg, fp16_src=fp16_src, offset=offset, seed=7,
                       what="%dx%d" % (M, N))
+
+
+@pytest.mark.parametrize("K", [1, 15, 16, 17, 31, 33, 47, 129, 1039, 2999])
+@pytest.mark.parametrize("fp16_src", [False, True])
+def test_few_token_rows_at_any_byte(K, fp16_src):
+    """The few-token GEMM, which none of the sizes above reaches."""
+    for p, q in ((2, 4), (3, 8)):
+        assert few_token(8, 4100, K, p, q, unpacked=True)
+        for offset in (0, 1, 5):
+            check(8, 4100, K, p, q, cfg=OPEN_XOR, fp16_src=fp16_src, offset=offset, seed=8, what="few tokens")

@@ -64,3 +64,13 @@ def test_tall_tiles_only_in_a_partly_filled_round():
     for s in ((1643, 7936, 5504, 7, 7), (1608, 7936, 9600, 7, 8)):
         c = apt.select_config(*s)
         assert (c.bm, c.bn) == (256, 128)
+
+
+@pytest.mark.parametrize("p,q,last", [(5, 5, 8192), (6, 6, 8192), (8, 8, 8192), (8, 4, 8192), (4, 8, 12288), (2, 8, 12288),
+                                      (4, 4, 16384)])
+def test_last_k_of_the_few_token_kernel(p, q, last):
+    """Its operands are held for all of K: past the last K that the registers hold, a
+    call of few tokens runs XOR + popcount."""
+    for unpacked in (False, True):
+        assert few_token(8, 4096, last, p, q, unpacked)
+        assert not few_token(8, 4096, last + 1, p, q, unpacked)
