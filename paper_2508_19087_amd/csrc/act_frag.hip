@@ -49,9 +49,6 @@ constexpr int kHeldIters = 4;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-// bytes of a six-bit fragment (32 rows of one word: 16 bytes per row, then 8;
-// gemm_int8.h's kSixBytes)
-constexpr int kSixBytes = 768;
 
 template <bool kHalf, bool kVec, int B>
 __global__ __launch_bounds__(kWave* kMaxWaves) void act_frag_kernel(

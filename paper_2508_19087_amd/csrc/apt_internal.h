@@ -126,8 +126,10 @@ hipError_t launch_gemm_xor_act(const GemmArgs& g, const void* a_src, bool fp16_s
 bool xor_act_sizes_ok(int M, int N, int K, int p, int q, const apt_config_t& cfg, bool fp16_src);
 
 // The few-token GEMM on the matrix cores (gemm_thin.hip): its modelled time,
-// infinity where it is not built for a problem (it takes M <= 128 on packed
-// activations, M <= 8 on unpacked ones), and its launches.  The XOR route runs
+// infinity where it is not built for a problem (it takes M <= 512 on packed
+// activations, M <= 8 on unpacked ones, and all of K in registers: K <= 16384 with
+// six-bit operands, 12288 with bytes, 8192 with weights of 5 to 8 bits), and its
+// launches.  The XOR route runs
 // it where the config leaves the launch shape to the library and it is the
 // faster of the two (thin_preferred).
 double thin_us(int M, int N, int K, int p, int q, bool unpacked);
@@ -157,7 +159,8 @@ hipError_t launch_act_frag(const void* src, bool fp16, int M, int K, int q, bool
 
 // Reassembled int8 MFMA route (gemm_int8.hip).  The workspace holds the
 // activations expanded into MFMA fragments (int8_workspace_bytes): from the
-// packed planes (src NULL), or, on the int8 route, from an unpacked source (g.a_rowsum and g.a_scale must then name src's outputs).
+// packed planes (src NULL), or, on the int8 route, from an unpacked source
+// (g.a_rowsum and g.a_scale must then name src's outputs).
 hipError_t launch_gemm_int8(const GemmArgs& g, const apt_config_t& cfg, void* workspace,
                             hipStream_t stream, const ActSource* src = nullptr);
 // Operand format of the activations in a config of the MFMA routes (0: int8).

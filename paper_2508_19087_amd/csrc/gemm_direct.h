@@ -56,7 +56,7 @@ constexpr int kBM = 128, kBN = 256;
 constexpr int kMF = kBM / 32, kNF = kBN / kWaves / 32;  // 32 x 32 blocks per wave
 constexpr int kPairWords = 8;                           // words of a chunk pair
 
-constexpr int kFrag = int8::kSixBytes;                  // LDS bytes of a fragment (32 rows of one word)
+constexpr int kFrag = kSixBytes;                  // LDS bytes of a fragment (32 rows of one word)
 
 template <int P>
 __global__ __launch_bounds__(kWaves* kWave, 2) void gemm_direct_kernel(Int8Params prm) {

@@ -91,7 +91,6 @@ constexpr int kStages = 3;                      // weight LDS ring depth
 // F = 5: the words u of at most 4 bits as six-bit E2M3 codes (u / 8) on both
 // sides (gemm_direct.h); a fragment is 32 rows of one word, 16 bytes per row and then 8 bytes per row.
 constexpr int kSixFormat = 5;
-constexpr int kSixBytes = 768;
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));

@@ -56,7 +56,12 @@ constexpr int kWaves = 8;
 constexpr int kTileN = 16;                    // weight rows per tile
 constexpr int kTileM = 16;                    // tokens per MFMA
 constexpr int kGroupChunks = 4;               // chunks per K group (one 16-byte vector per lane)
-constexpr int kNT = 2;                        // weight loads are non-temporal: read once per call
+// Weight loads are non-temporal: one row of workgroups reads them once per call.
+// With several rows (more tokens than one workgroup holds) the caches serve the
+// re-reads all the same: against plain loads equal within 1% up to 4 rows, 2%
+// slower with 5 to 16 (40 to 512 tokens, 150 problems), which does not pay for a
+// second instance of every kernel.
+constexpr int kNT = 2;
 constexpr int kRedStride = 20;                // dwords per token row of a tile's partial sums in LDS
 
 enum { kLow = 0, kByte = 1, kByte8 = 2 };
@@ -78,7 +83,6 @@ struct ThinParams {
   int src;
   int a_vec;         // 16-byte source loads allowed
   uint16_t* a_scale_out;
-  int run;           // most tiles of a workgroup (the LDS copy of the column scales)
   int rows_off;      // byte offset of the converted rows in LDS
   int ones;          // byte offset of 32 bytes of ones, from the rows
 };

@@ -61,7 +61,6 @@ hipError_t launch(const GemmArgs& g, const void* a_src, int src, uint16_t* a_sca
   prm.src = src;
   prm.a_vec = (reinterpret_cast<uintptr_t>(a_src) & 15u) == 0 && g.K % 16 == 0;
   prm.a_scale_out = a_scale_out;
-  prm.run = L.run;
   prm.rows_off = L.rows_off;
   prm.ones = prm.nchunks * kChunk * g.M;
   switch (g.p) {

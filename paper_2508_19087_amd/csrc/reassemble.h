@@ -17,7 +17,7 @@
 // The rebuild is a 3-level merge tree: pairs of planes -> 2-bit fields
 // (elements at even / odd bit positions), pairs of those -> nibbles, then
 // nibbles -> bytes.  Each merge is a shift plus a bit-field select
-// (v_bfi_b32).  With b <= 4 the top level only splits nibbles into bytes.
+// (v_bitop3_b32).  With b <= 4 the top level only splits nibbles into bytes.
 // Missing planes (i >= b) are zero and fold away at compile time.
 #pragma once
 
@@ -191,6 +191,10 @@ __device__ __forceinline__ void fp6_word(const uint32_t* pw, uint32_t out[6]) {
   out[4] = (y[5] >> 8) | (y[6] << 16);
   out[5] = (y[6] >> 16) | (y[7] << 8);
 }
+
+// Bytes of a fragment of six-bit operands: 32 rows of one word, 16 bytes of each row
+// and then 8 of each.
+constexpr int kSixBytes = 768;
 
 // Packed six-bit fields of the 32 elements of six code planes c[0..5] (bit i
 // of an element's field in plane i): 192 bits in out[0..5], the operand order
