@@ -41,11 +41,13 @@ if ROOT not in sys.path:
 
 METRIC = "effective TOPS and % of int8-MFMA/HBM roofline for WpAq GEMM, M=1 & M=2048"
 PEAK_INT8_TOPS = 5000.0     # MI355X dense int8 MFMA, 5.0 POP/s
+PEAK_SIX_BIT_TOPS = 10000.0  # dense six-bit operands of the block-scaled MFMA, twice the int8 rate
 PEAK_HBM_GBS = 8000.0       # MI355X HBM3E, 8 TB/s
 MALL_BYTES = 256 << 20      # Infinity Cache; cold-weight runs rotate through > 2x this
 PROFILES = os.path.join(ROOT, "profiles")
 KERNEL_SOURCES = ["paper_2508_19087_amd/csrc/gemm_int8.h", "paper_2508_19087_amd/csrc/gemm_int8.hip",
-                  "paper_2508_19087_amd/csrc/gemm_int8_inst.hip", "paper_2508_19087_amd/csrc/reassemble.h",
+                  "paper_2508_19087_amd/csrc/gemm_int8_inst.hip", "paper_2508_19087_amd/csrc/gemm_direct.h",
+                  "paper_2508_19087_amd/csrc/gemm_direct_inst.hip", "paper_2508_19087_amd/csrc/reassemble.h",
                   "paper_2508_19087_amd/csrc/select.hip", "paper_2508_19087_amd/csrc/act_frag.hip",
                   "paper_2508_19087_amd/csrc/rowcode.h"]
 
@@ -1243,13 +1245,11 @@ def paper_shapes(calls: int = 100, reps: int = 3):
 
 def xor_crossover(calls: int = 50):
     """Where the XOR route beats the MFMA routes: for M = 16..256 and a few
-    (N, K, p, q), the forced XOR route (its own launch shape) and
-    the best of the 128x128 MFMA configs the model takes at such sizes (int8,
-    and FP4 where it applies; one workgroup per tile and 512 workgroups), each
-    as one HIP graph of `calls` calls (warm, int32 output), plus the selected
-    config; then the least-squares fit of the XOR model the selector uses."""
-    import math
-
+    (N, K, p, q), the forced XOR route (its own launch shape and choice between
+    XOR + popcount and the few-token GEMM) and the best of the 128x128 MFMA
+    configs the model takes at such sizes (int8, and FP4 where it applies; one
+    workgroup per tile and 512 workgroups), each as one HIP graph of `calls`
+    calls (warm, int32 output), plus the selected config."""
     import numpy as np
     import torch
 
@@ -1296,20 +1296,16 @@ def xor_crossover(calls: int = 50):
                              "mfma_128x128_us": round(mfma, 2), "selected": apt.ROUTE_NAMES[sel.route],
                              "selected_us": round(selected, 2)})
             log("bench: xor crossover N=%d K=%d W%dA%d done" % (N, K, p, q))
-    # the selector's XOR model: t = t0 + W (a + b q + c p q), W = 8 ceil(M / 8) N K / 32 word pairs
-    # (8 activation rows per block row), fitted by least squares on the relative error
-    t = np.array([r["xor_us"] for r in rows])
-    W = np.array([8 * math.ceil(r["M"] / 8) * r["N"] * r["K"] / 32 for r in rows]) * 1e-6
-    q = np.array([r["q"] for r in rows], dtype=float)
-    pq = np.array([r["p"] * r["q"] for r in rows], dtype=float)
-    X = np.vstack([np.ones_like(W), W, W * q, W * pq]).T
-    coef = np.linalg.lstsq(X / t[:, None], np.ones_like(t), rcond=None)[0]
-    err = np.abs(X @ coef / t - 1)
-    return {"rows": rows, "xor_fit": {"t0_us": round(coef[0], 3), "a_ps_per_word": round(coef[1], 4),
-                                      "b_ps_per_word_per_q": round(coef[2], 4),
-                                      "c_ps_per_word_per_pq": round(coef[3], 4),
-                                      "median_rel_err": round(float(np.median(err)), 3),
-                                      "max_rel_err": round(float(err.max()), 3)}}
+    return {"rows": rows}
+
+
+def runs_six_bit(c, K, p, q):
+    """Whether config c runs gemm_direct.h's kernel (six-bit operands) in place of
+    the int8 route's own: 256 x 128 tiles with 4 x 1 waves, no split, operands of at
+    most 4 bits and sums below 2^24."""
+    import paper_2508_19087_amd as apt
+    return (c.route == apt.APT_ROUTE_INT8_MFMA and (c.bm, c.bn, c.waves_m, c.waves_n) == (256, 128, 4, 1)
+            and c.split_n == 0 and p <= 4 and q <= 4 and K * ((1 << p) - 1) * ((1 << q) - 1) < 1 << 24)
 
 
 def stored_traffic():
@@ -1708,7 +1704,7 @@ def write_traffic(fetch_dir: str, write_dir: str, commands: str):
         factor = COPY_BYTES / statistics.median(copy)
         # the GEMM's kernels: every dispatch after the warm-up call
         gemm = {k: vs for k, vs in vals.items()
-                if "expand_a_kernel" in k or "act_frag_kernel" in k or "gemm_int8_" in k}
+                if any(n in k for n in ("expand_a_kernel", "act_frag_kernel", "gemm_int8_", "gemm_direct_"))}
         per_call = 0.0
         kernels = {}
         for k, vs in gemm.items():
@@ -1749,7 +1745,7 @@ def main():
                     help="print the model's and the search module's config for every workload "
                          "shape, with their times, and exit")
     ap.add_argument("--xor-crossover", action="store_true",
-                    help="print the XOR route against the MFMA routes for small M, with the XOR model fit, and exit")
+                    help="print the XOR route against the MFMA routes for small M and exit")
     ap.add_argument("--paper-shapes", action="store_true",
                     help="print this library's times at the shapes of the paper's kernel tables and exit")
     ap.add_argument("--epilogues", action="store_true",
@@ -1918,12 +1914,19 @@ def main():
         tiles += " over columns [0, %d) and %dx%d tiles over the rest" % (sel.split_n, sel.tail_bm,
                                                                           sel.tail_bn)
     tiles += ", one workgroup per tile" if sel.grid == 0 else ", %d persistent workgroups" % sel.grid
+    gemm_kernel, operands, operand_peak = "gemm_int8 kernel", "int8", PEAK_INT8_TOPS
+    if runs_six_bit(sel, pre.K, pre.p, pre.q):
+        gemm_kernel, operands, operand_peak = "gemm_direct kernel", "six-bit E2M3 codes", PEAK_SIX_BIT_TOPS
+        tiles = "128x256 tiles, one workgroup per tile"
+    # the metric relates to the int8 MFMA rate; operand_* to the rate of the operands that run
     roofline = {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_INT8_TOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / PEAK_INT8_TOPS, 4), "traffic": traffic,
+                "operands": operands, "operand_peak": operand_peak,
+                "operand_frac": round(achieved / operand_peak, 4),
                 "kernel": ("apt_gemm W4A4 M=2048 N=11008 K=4096 on packed activations: expand_a_kernel"
                            if wl.packed_prefill else
                            "apt_gemm_act W4A4 M=2048 N=11008 K=4096 from the int8 codes: act_frag_kernel")
-                          + " + gemm_int8 kernel (%s), %d back-to-back calls" % (tiles, args.roofline_calls),
+                          + " + %s (%s), %d back-to-back calls" % (gemm_kernel, tiles, args.roofline_calls),
                 "avg_launch_us": round(gemm_s * 1e6, 2)}
     result = {
         "metric": METRIC, "value": round(wl.ops / step_s / 1e12, 3), "unit": "TOPS",
@@ -1942,7 +1945,7 @@ def main():
                    "decode_activations": ("packer + apt_gemm" if wl.unfused_decode else
                                           "apt_gemm_decode (converted inside the GEMV)"),
                    "prefill_activations": ("packer + apt_gemm" if wl.packed_prefill else
-                                           "apt_gemm_act (codes written straight into the int8 "
+                                           "apt_gemm_act (codes written straight into the "
                                            "MFMA fragments)"),
                    "prefill_config": cfg,
                    "prefill_config_two_batches": (wl.pre_cfg_two.as_dict()
