@@ -304,7 +304,15 @@ __global__ __launch_bounds__(kWave* kMaxWaves, min_waves(P, Q, MT, DEEP, SRC)) v
     for (int m = 0; m < kSrcRows; ++m) {
       if (m >= mrows) break;  // uniform
       rowcode::Quantizer qz{};
-      if (SRC == kSrcHalf) qz = s_qz[m].uniform(Q);
+      if (SRC == kSrcHalf) {
+        if (Q <= 2) {
+          qz = s_qz[m].uniform(Q);
+        } else {  // (enough registers; 0.5% faster at one token W2A4)
+          qz = s_qz[m];
+          qz.b = Q;
+          qz.quick = __builtin_amdgcn_readfirstlane(qz.quick);
+        }
+      }
 #pragma unroll
       for (int r = 0; r < kHeld; ++r)
         if (r < src_rounds) convert(m, r, sd[m][r], qz);
