@@ -84,9 +84,10 @@ hipError_t launch(const GemmArgs& g, const void* a_src, int src, uint16_t* a_sca
 // and the MFMAs of each token tile) and the weight stream (re-reads by further
 // rows of workgroups are served by the caches).  Least squares on the relative
 // error over cold timings on MI355X: six-bit operands M = 2..512, N and K =
-// 512..11008 (median error 6%); bytes 651 problems with M = 2..512, N = 128..22016, K =
-// 128..8192, weights of 1 to 8 bits (median error 5%, up to 32 rows of workgroups
-// among them: W4A8 400 x 1024 x 8192 18 us modelled, 16.4 measured).
+// 512..11008 (median error 6%); bytes M = 2..512, N = 128..22016, K = 128..8192,
+// weights of 1 to 8 bits (median error 5% over 1405 problems, up to 32 rows of
+// workgroups among them: W4A8 400 x 1024 x 8192 17.6 us modelled, 16.4 measured;
+// a word of 1 bit costs what one of 2 does).
 double thin_us(int M, int N, int K, int p, int q, bool unpacked) {
   ThinLaunch L;
   if (!plan(M, N, K, p, q, unpacked ? thin::kSrcHalf : thin::kSrcPacked, &L)) return HUGE_VAL;
@@ -94,7 +95,7 @@ double thin_us(int M, int N, int K, int p, int q, bool unpacked) {
   constexpr double kRebuild[5] = {0, 7, 10, 18, 22};
   return L.cls == thin::kLow
              ? 2.61 + 0.886 * ops + items * (0.0115 * kRebuild[p] + 0.233 * L.mt) + 0.178 * mb
-             : 2.96 + 1.35 * ops + items * (0.119 * p + 0.284 * L.mt) + 0.071 * mb;
+             : 3.26 + 1.28 * ops + items * (0.106 * std::max(p, 2) + 0.287 * L.mt) + 0.085 * mb;
 }
 
 hipError_t launch_gemm_thin(const GemmArgs& g, hipStream_t s) {

@@ -437,10 +437,13 @@ apt_config_t select_config(int M, int N, int K, int p, int q) {
   // costs.  The MFMA figures were measured with every compute unit
   // busy and overstate grids of a few tiles by 10-40%, so they count at 90%
   // here (measured over M = 16..256, N, K = 1024..14336, p*q = 2..16).
+  // The few-token kernel's byte operands have to win by 0.5 us more: calls on fp32 or
+  // fp16 activations pack them in a launch of their own there (W1A8 391 x 3584 x 7424
+  // from fp32 44 us against 36; of 1500 problems 7 instead of 14 lose 7% or more).
   const apt_config_t open = base_config(APT_ROUTE_XOR);
   const double few = thin_preferred(M, N, K, p, q, open, false) ? thin_us(M, N, K, p, q, false)
                                                                 : model_xor_us(M, N, K, p, q);
-  if (few < 0.9 * best) return open;
+  if (few + (p > 4 || q > 4 ? 0.5 : 0.0) < 0.9 * best) return open;
   const Int8Shape& s = kInt8Shapes[best_i];
   apt_config_t c = base_config(best_fp4 ? APT_ROUTE_FP4_MFMA : APT_ROUTE_INT8_MFMA);
   c.bm = s.bm;
